@@ -69,8 +69,8 @@ struct AttnParams {
   const void* seg_vbase[kMaxSeg];
 };
 
-// Query rows per workgroup of each attention kernel (the host sizes the grid with
-// these) and keys per key tile of the bf16 kernel.
+// Query rows per workgroup of the bf16 attention kernel (the host sizes the grid with it) and
+// the most of the fp32 one (its launcher picks 64, 32 or 16), and keys per key tile of the bf16 kernel.
 constexpr int kAttnBf16BM = 256;
 constexpr int kAttnBf16BN = 64;
 // Largest K/V row stride (elements) of the bf16 attention: a key tile spans 64 rows, addressed
