@@ -12,34 +12,34 @@
 // O^T += V^T P^T directly as the B operand; the V^T A operand is read from the
 // row-major V tile with ds_read_b64_tr_b16 (LDS transpose read).
 //
-// Software pipeline (per wavefront): iteration j issues the 16 MFMAs of S_{j+1}
-// with the probabilities of S_j pairs 0..9 formed under them (phase A), then
-// the 16 MFMAs of O += V_j^T P_j^T, under the first eight of which the remaining
-// pairs 10..15 are formed (phase B). A pair takes three MFMA slots (exponent
-// arguments, exponentials, row-sum adds and bf16 pack), so the instructions of
-// one slot never wait on each other. sched_barrier fences keep that order, so
-// the vector ALU works while the matrix core runs. K tiles run one
-// tile ahead of V tiles through two LDS buffers each. At the start of phase B of
+// Software pipeline (per wavefront), three tiles deep: iteration j issues the MFMAs of
+// O += V_{j-1}^T P_{j-1}^T, then those of S_{j+1}, and forms the 16 probability pairs of S_j
+// under them. The three do not depend on each other, so the vector ALU works evenly under
+// all the MFMAs of a tile and one bound test a tile suffices. A pair takes three steps spread
+// over the MFMA slots (exponent arguments, exponentials, row-sum adds and bf16 pack), so the
+// instructions of one step never wait on each other; sched_barrier fences keep that order.
+// Against two phases a tile (S_{j+1} with pairs 0..9, then O += V_j^T P_j^T with the rest, each
+// with its own operand latency and bound test): 2.82 -> 2.75 ms at 24 heads of 128, 16640 queries
+// and keys (1.21 -> 1.24 PFLOP/s; a large library product reaches 1.27), 486 -> 460 us at 24 heads
+// of 64, 8448 queries and keys.
+// K tiles run two tiles ahead of V tiles through two LDS buffers each. Half-way through
 // iteration j direct global-to-LDS loads (no staging registers, no LDS store
-// instructions) fill the buffers that held K_j and V_{j-1} with K_{j+2} and
-// V_{j+1}; the iteration's one barrier, after a wait for those loads, publishes
+// instructions) fill the buffers that held K_j and V_{j-2} with K_{j+2} and
+// V_j; the iteration's one barrier, after a wait for those loads, publishes
 // them.
 //
 // One workgroup fills a CU with two wavefronts per SIMD (at most 256 vector
 // registers per lane each): while one wavefront forms probabilities the other
 // keeps the matrix core busy, and the eight wavefronts share every K/V tile
-// in LDS (each wavefront loads two 1 KiB blocks of each tile). s_setprio
-// alternates which wavefront of a SIMD wins issue ties between the phases, so
-// the pair finishes a tile together instead of one idling at the barrier.
+// in LDS (each wavefront loads two 1 KiB blocks of each tile).
 //
 // Online softmax in the exp2 domain without a per-tile row max: probabilities
 // are formed against the running max m, and a lane's partial row sum bounds
 // each of its terms, so a sum within 2^12 proves that every probability is at
 // most 2^12 and m may stay. The test runs (wave-wide, NaN and inf failing it)
-// once for pairs 0..9 before any of them enters O and once for pairs 8..15
-// (P blocks 2 and 3) before the first MFMA that reads them; when it fails (always at a
+// once a tile, before any of its probabilities enters O; when it fails (always at a
 // workgroup's first tile, where m = -inf), a cold path takes the row max of
-// the scores still to be formed, rescales O and l, and forms them again. The
+// the scores, rescales O and l, and forms the probabilities again. The
 // O rescale and the row max are thus almost never executed.
 // Row sums add the fp32 probabilities, so the reference mass and the
 // log-sum-exp carry no bf16 rounding. O is divided by a second sum, that of
@@ -88,7 +88,8 @@ typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
 constexpr int BM = kAttnBf16BM;  // query rows per workgroup
 constexpr int BN = kAttnBf16BN;  // keys per LDS tile
-constexpr int NT = 512;          // threads per workgroup
+constexpr int NW = BM / 32;      // wavefronts per workgroup
+constexpr int NT = 64 * NW;      // threads per workgroup
 constexpr float PBOUND = 4096.0f;  // bound on a probability against the running max (2^12)
 
 // Row permutation of a 32-key MFMA block: swaps bits 2 and 3 of the row index.
@@ -132,12 +133,12 @@ __device__ __forceinline__ float add_bf16x2(uint32_t w, float acc) {
 //     dims 32 db .. 32 db + 31, with the dim offset XORed by 16 when b(r, 1) is set,
 //     which makes the transpose reads of the V^T operand conflict-free.
 // No padding, no staging registers and no LDS store instructions: a tile's loads are
-// issued about a phase B ahead of the barrier that publishes it.
+// issued half an iteration ahead of the barrier that publishes it.
 template <int D>
 struct Layout {
   static constexpr int NB = D / 8;        // 1 KiB blocks per K or V tile
   static constexpr int TILE = NB * 512;   // elements per tile
-  static constexpr int NLD = NB / 8;      // blocks each of the 8 wavefronts loads per tile
+  static constexpr int NLD = NB / NW;     // blocks each wavefront loads per tile
 };
 
 // Buffer resource of one K or V tile: base = its first row, range = its valid rows, so
@@ -162,21 +163,6 @@ __device__ __forceinline__ uint32_t dma_lane_offset(int lane, int64_t ss) {
   return (uint32_t)((lane >> 2) * ss * 2 + 16 * ((lane & 3) ^ (((lane >> 3) & 1) << 1)));
 }
 
-// This wavefront's blocks of one K or V tile, straight into the LDS tile.
-template <int D, bool IS_K>
-__device__ __forceinline__ void tile_dma(uint16_t* tile, __amdgpu_buffer_rsrc_t rs, uint32_t voff, int64_t ss,
-                                         int wave) {
-  constexpr int KS = D / 16, DB = D / 32;
-#pragma unroll
-  for (int i = 0; i < Layout<D>::NLD; ++i) {
-    const int blk = wave + 8 * i;
-    const int64_t soff = IS_K ? (int64_t)(blk / KS) * 32 * ss * 2 + (blk % KS) * 32
-                              : (int64_t)(blk / DB) * 16 * ss * 2 + (blk % DB) * 64;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(tile + blk * 512), 16,
-                                             voff, __builtin_amdgcn_readfirstlane((uint32_t)soff), 0, 0);
-  }
-}
-
 // Direct-load cursor of one K or V stream: the next key tile to load, the first row of that
 // tile, the rows of its view from there on, and the view's row stride, lane offset and the
 // scalar offsets of this wavefront's blocks. Advancing to the next tile costs a 64-bit add;
@@ -199,7 +185,7 @@ struct DmaCursor {
     t = tile0;
 #pragma unroll
     for (int i = 0; i < Layout<D>::NLD; ++i) {
-      const int blk = wave + 8 * i;
+      const int blk = wave + NW * i;
       soff[i] = __builtin_amdgcn_readfirstlane(
           (uint32_t)(IS_K ? (int64_t)(blk / KS) * 32 * ss * 2 + (blk % KS) * 32
                           : (int64_t)(blk / DB) * 16 * ss * 2 + (blk % DB) * 64));
@@ -211,7 +197,7 @@ struct DmaCursor {
     const __amdgpu_buffer_rsrc_t rs = tile_rsrc<D>(ptr, ss, valid);
 #pragma unroll
     for (int i = 0; i < Layout<D>::NLD; ++i) {
-      const int blk = wave + 8 * i;
+      const int blk = wave + NW * i;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(tile + blk * 512), 16,
                                                voff, soff[i], 0, 0);
     }
@@ -316,56 +302,7 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnParams p) {
   const uint32_t voff_rv = dma_lane_offset<false>(lane, vrv.ss);
   const uint32_t voff_yk = dma_lane_offset<true>(lane, p.k_tgt.ss);
   const uint32_t voff_yv = dma_lane_offset<false>(lane, p.v_tgt.ss);
-  // SEG: each of the K and V streams visits reference tiles in increasing order, so it keeps
-  // its current segment, that segment's base pointer (this (b, h) applied) and end tile, and
-  // reads the next ones from the kernel arguments only when it crosses a segment end.
-  int kseg = 0, kend = 0, vseg = 0, vend = 0;
-  const uint16_t *kbase = nullptr, *vbase = nullptr;
-  const int64_t kbh = b * krv.sb + h * krv.sh, vbh = b * vrv.sb + h * vrv.sh;
-  if constexpr (SEG) {
-    kend = vend = p.seg_tile_end[0];
-    kbase = static_cast<const uint16_t*>(p.seg_kbase[0]) + kbh;
-    vbase = static_cast<const uint16_t*>(p.seg_vbase[0]) + vbh;
-  }
-  // Loads reference tile j of one of K, V (strides ss, lane offset voff) from the base of
-  // its segment into an LDS tile.
-  auto load_ref_seg = [&](auto is_k, uint16_t* dst, int j, int& seg, int& end, const uint16_t*& base,
-                          const void* const* seg_base, int64_t bh_off, int64_t ss, uint32_t voff) {
-    while (j >= end && seg + 1 < p.n_seg) {
-      end = p.seg_tile_end[++seg];
-      base = static_cast<const uint16_t*>(seg_base[seg]) + bh_off;
-    }
-    tile_dma<D, decltype(is_k)::value>(dst, tile_rsrc<D>(base + (int64_t)j * BN * ss, ss, tile_valid(j)), voff, ss,
-                                       wave_u);
-  };
-  auto load_k = [&](uint16_t* dst, int j) {
-    const int valid = tile_valid(j);
-    if constexpr (SEG) {
-      if (j < n_rt) {
-        load_ref_seg(std::true_type{}, dst, j, kseg, kend, kbase, p.seg_kbase, kbh, krv.ss, voff_r);
-        return;
-      }
-    }
-    if (j < n_rt)
-      tile_dma<D, true>(dst, tile_rsrc<D>(kr + (int64_t)j * BN * kr_ss, kr_ss, valid), voff_r, kr_ss, wave_u);
-    else
-      tile_dma<D, true>(dst, tile_rsrc<D>(ky + (int64_t)(j - n_rt) * BN * ky_ss, ky_ss, valid), voff_yk, ky_ss,
-                        wave_u);
-  };
-  auto load_v = [&](uint16_t* dst, int j) {
-    const int valid = tile_valid(j);
-    if constexpr (SEG) {
-      if (j < n_rt) {
-        load_ref_seg(std::false_type{}, dst, j, vseg, vend, vbase, p.seg_vbase, vbh, vrv.ss, voff_rv);
-        return;
-      }
-    }
-    if (j < n_rt)
-      tile_dma<D, false>(dst, tile_rsrc<D>(vr + (int64_t)j * BN * vr_ss, vr_ss, valid), voff_rv, vr_ss, wave_u);
-    else
-      tile_dma<D, false>(dst, tile_rsrc<D>(vy + (int64_t)(j - n_rt) * BN * vy_ss, vy_ss, valid), voff_yv, vy_ss,
-                         wave_u);
-  };
+  const int64_t kbh = b * krv.sb + h * krv.sh, vbh = b * vrv.sb + h * vrv.sh;  // SEG: this (b, h)
 
   // ---- this lane's query row; Q^T as the B operand (query n, head-dim chunk 2*kk + g)
   const int qrow = qt * BM + wave * 32 + n;
@@ -385,24 +322,7 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnParams p) {
   const int tr_i = lane & 15, tr_G = lane >> 4;         // 16-lane group of the transpose read
   const int v_lane = 32 * (8 * (tr_G >> 1) + (tr_i >> 2)) + ((16 * (tr_G & 1) + 4 * (tr_i & 3)) ^ (16 * ((tr_i >> 3) & 1)));
 
-  // ---- prologue: K_{j0}, K_{j0+1} and V_{j0} into LDS; S_{j0}. Tile j lives in
-  // buffer (j - j0) & 1.
-  load_k(kbuf0, j0);
-  load_v(vbuf0, j0);
-  if (j0 + 1 < j1) load_k(kbuf1, j0 + 1);
-  __syncthreads();
-  f32x16 sa[2], sb[2];
-#pragma unroll
-  for (int mb = 0; mb < 2; ++mb) {
-    sa[mb] = f32x16{};
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      const bf16x8 a = *reinterpret_cast<const bf16x8*>(kbuf0 + k_lane + 512 * (KS * mb + kk));
-      sa[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qreg[kk], sa[mb], 0, 0, 0);
-    }
-  }
-  __syncthreads();  // every wavefront has read K_{j0} before the first iteration refills its buffer
-  // cursors of the in-loop loads: K from tile j0 + 2, V from tile j0 + 1
+  // ---- the load cursors of the K and V streams
   DmaCursor<D, true> kc;
   DmaCursor<D, false> vc;
   // SEG: the segment each cursor reads and the key tile that ends it. A cursor re-targets to
@@ -443,8 +363,33 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnParams p) {
     cur.ptr = reinterpret_cast<const uint16_t*>(reinterpret_cast<const char*>(cur.ptr) +
                                                 (static_cast<const char*>(tab[sg]) - from));
   };
-  cursor_view(std::true_type{}, kc, j0 + 2);
-  cursor_view(std::false_type{}, vc, j0 + 1);
+  cursor_view(std::true_type{}, kc, j0);
+  cursor_view(std::false_type{}, vc, j0);
+  auto issue_load = [&](auto is_kc, auto& cur, uint16_t* dst) __attribute__((always_inline)) {
+    constexpr bool IS_K = decltype(is_kc)::value;
+    if (cur.t == n_rt) {
+      cursor_view(is_kc, cur, cur.t);
+    } else if constexpr (SEG) {
+      if (cur.t == (IS_K ? kc_end : vc_end)) cursor_next_seg(is_kc, cur);
+    }
+    cur.load(dst, wave_u);
+  };
+
+  // ---- prologue: K_{j0} and K_{j0+1} into LDS; S_{j0}. Tile j lives in buffer (j - j0) & 1.
+  issue_load(std::true_type{}, kc, kbuf0);
+  if (j0 + 1 < j1) issue_load(std::true_type{}, kc, kbuf1);
+  __syncthreads();
+  f32x16 sa[2], sb[2];
+#pragma unroll
+  for (int mb = 0; mb < 2; ++mb) {
+    sa[mb] = f32x16{};
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+      const bf16x8 a = *reinterpret_cast<const bf16x8*>(kbuf0 + k_lane + 512 * (KS * mb + kk));
+      sa[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qreg[kk], sa[mb], 0, 0, 0);
+    }
+  }
+  __syncthreads();  // every wavefront has read K_{j0} before the first iteration refills its buffer
 
   f32x16 o[DB];
 #pragma unroll
@@ -487,16 +432,18 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnParams p) {
     seg_end_t = seg_idx < p.n_seg ? seg_end_tab[seg_idx] : -1;
   };
 
-  // jbc: the LDS buffer of K_j and V_j, (j - j0) & 1, as a compile-time constant.
-  auto iteration = [&](auto jbc, int j, f32x16(&s_cur)[2], f32x16(&s_next)[2]) {
+  // jbc: the LDS buffer of K_j and V_j, (j - j0) & 1, as a compile-time constant. firstc: the
+  // workgroup's first tile, which has no earlier probabilities to multiply with V.
+  auto iteration = [&](auto jbc, auto firstc, int j, f32x16(&s_cur)[2], f32x16(&s_next)[2], uint32_t(&p_prev)[4][4],
+                       uint32_t(&p_cur)[4][4]) __attribute__((always_inline)) {
     constexpr int jb = decltype(jbc)::value;
-    // Global loads for the tiles this iteration stages: K_{j+2} and V_{j+1}, issued at the
-    // start of phase B through the K and V cursors; past the workgroup's last key tile the
-    // cursors skip the load.
+    constexpr bool FIRST = decltype(firstc)::value;
+    constexpr int PV = FIRST ? 0 : NPV;  // MFMAs of O += V_{j-1}^T P_{j-1}^T
+    constexpr int NS = PV + NQK;         // MFMA slots
     uint16_t* const kb_cur = jb ? kbuf1 : kbuf0;   // K_j (already read), refilled with K_{j+2}
     uint16_t* const kb_next = jb ? kbuf0 : kbuf1;  // K_{j+1}
-    uint16_t* const vb_cur = jb ? vbuf1 : vbuf0;   // V_j
-    uint16_t* const vb_next = jb ? vbuf0 : vbuf1;  // V_{j-1} (already read), refilled with V_{j+1}
+    uint16_t* const vb_cur = jb ? vbuf1 : vbuf0;   // V_{j-2} (already read), refilled with V_j
+    uint16_t* const vb_prev = jb ? vbuf0 : vbuf1;  // V_{j-1}
 
     // The ragged last tile of each of the reference and target segments (if any) is known
     // up front: the test in the loop compares tile indices only.
@@ -510,23 +457,33 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnParams p) {
           if (key >= valid) s_cur[mb][r] = -__builtin_inff();
         }
     }
-
-    // Issue priority: the first wavefront on a SIMD (waves 0-3) otherwise wins every tie,
-    // finishes its tile early and waits at the barrier while its partner runs alone. The
-    // partner gets the higher priority in phase A and the first one in phase B.
-    const bool partner = __builtin_amdgcn_readfirstlane(wave) >= 4;
-    if (partner) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0);
-    // ---- phase A: the MFMAs of S_{j+1} (K_{j+1} is in LDS), with the probability pairs 0..9
-    // of S_j (P blocks 0, 1 and half of block 2) formed under them, three slots per pair.
-    // At the last iteration the K buffer holds no tile and S_{j+1} is discarded.
-    const uint16_t* kb = kb_next;
-    auto k_operand = [&](int i) {  // i = KS * mb + kk
-      return *reinterpret_cast<const bf16x8*>(kb + k_lane + 512 * i);
+    // The next tiles' direct loads, issued half-way, where the V operand reads end: at the
+    // iteration's start or three quarters through it the launch was 2% and 4% slower.
+    auto issue_loads = [&]() __attribute__((always_inline)) {
+      if (kc.t < j1) issue_load(std::true_type{}, kc, kb_cur);
+      issue_load(std::false_type{}, vc, vb_cur);
     };
-    uint32_t pw[4][4];  // packed bf16 probabilities: P block s2, keys 16*s2 + 8*g + 2w, +1
+    // Head dim 64: which wavefront of a SIMD wins issue ties alternates between the two halves, so
+    // the pair finishes a tile together instead of one idling at the barrier (-1%; at head dim
+    // 128 it made no difference).
+    const bool partner = wave_u >= 4;
+    auto set_prio = [](bool high) __attribute__((always_inline)) {
+      if (high)
+        __builtin_amdgcn_s_setprio(1);
+      else
+        __builtin_amdgcn_s_setprio(0);
+    };
+    auto k_operand = [&](int i) {  // i = KS * mb + kk
+      return *reinterpret_cast<const bf16x8*>(kb_next + k_lane + 512 * i);
+    };
+    auto v_operand = [&](int i) {  // i = DB * s2 + db
+      const uint16_t* a = vb_prev + v_lane + 512 * i;
+      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(a));
+      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(a + 128));
+      return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
     // Row-sum chains: pairs 0..7 (P blocks 0, 1) and pairs 8..15 (P blocks 2, 3).
     float rs_a = 0.f, rs_b = 0.f, m_new = m_run;
-    float a01 = 1.f;  // rescale of P blocks 0 and 1 by the second bound test
     // Adds a pair to its row-sum chain; the first pair of a chain starts it (0 + x is not
     // folded away: it would turn -0 into +0).
     auto row_add = [&](int q, float e0, float e1) {
@@ -538,41 +495,31 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnParams p) {
         pin(rs_b);
       }
     };
-    auto prob_pair = [&](int q) {  // scores 2q, 2q+1 -> P block q/4, word q%4
-      const int mb = q >> 3, o2 = (2 * q) & 15;
-      const float e0 = __builtin_amdgcn_exp2f(fmaf(s_cur[mb][o2], c, -m_new));
-      const float e1 = __builtin_amdgcn_exp2f(fmaf(s_cur[mb][o2 + 1], c, -m_new));
-      row_add(q, e0, e1);
+    auto pack = [&](int q, float e0, float e1) {  // P block q/4, word q%4
       bf16x2 pr;
       pr[0] = (__bf16)e0;
       pr[1] = (__bf16)e1;
       uint32_t w = __builtin_bit_cast(uint32_t, pr);
       pin(w);
-      pw[q >> 2][q & 3] = w;
+      p_cur[q >> 2][q & 3] = w;
     };
-    // Software pipeline of the pairs over the MFMA slots: a slot forms the exponent
+    // Software pipeline of the pairs over the MFMA slots: a step forms the exponent
     // arguments of pair k, the exponentials of pair k - 1 and the row-sum adds and bf16 pack
-    // of pair k - 2, so no instruction of a slot waits on another of the same slot.
-    float pa0 = 0.f, pa1 = 0.f;  // exponent arguments of the pair started one slot earlier
-    float pe0 = 0.f, pe1 = 0.f;  // exponentials of the pair started two slots earlier
-    auto pair_fin = [&](int q) {
-      row_add(q, pe0, pe1);
-      bf16x2 pr;
-      pr[0] = (__bf16)pe0;
-      pr[1] = (__bf16)pe1;
-      uint32_t w = __builtin_bit_cast(uint32_t, pr);
-      pin(w);
-      pw[q >> 2][q & 3] = w;
-    };
-    auto pipe_slot = [&](int k, int lo, int hi) {  // pairs lo..hi-1
-      if (k - 2 >= lo && k - 2 < hi) pair_fin(k - 2);
-      if (k - 1 >= lo && k - 1 < hi) {
+    // of pair k - 2, so no instruction of a step waits on another of the same step.
+    float pa0 = 0.f, pa1 = 0.f;  // exponent arguments of the pair started one step earlier
+    float pe0 = 0.f, pe1 = 0.f;  // exponentials of the pair started two steps earlier
+    auto pipe_step = [&](int k) {
+      if (k >= 2) {
+        row_add(k - 2, pe0, pe1);
+        pack(k - 2, pe0, pe1);
+      }
+      if (k >= 1 && k < 17) {
         pe0 = __builtin_amdgcn_exp2f(pa0);
         pe1 = __builtin_amdgcn_exp2f(pa1);
         pin(pe0);
         pin(pe1);
       }
-      if (k >= lo && k < hi) {
+      if (k < 16) {
         const int mb = k >> 3, o2 = (2 * k) & 15;
         pa0 = fmaf(s_cur[mb][o2], c, -m_new);
         pa1 = fmaf(s_cur[mb][o2 + 1], c, -m_new);
@@ -580,115 +527,66 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnParams p) {
         pin(pa1);
       }
     };
-    // Row max of the lane's scores in key blocks mb0..1, shared by the lane pair of a query.
-    auto tile_max = [&](int mb0) {
-      float m = s_cur[1][0];
-      pin(m);  // keeps the reduction in the cold path (it was otherwise begun in the hot block)
-#pragma unroll
-      for (int r = 1; r < 16; ++r) m = fmaxf(m, s_cur[1][r]);
-      if (mb0 == 0) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) m = fmaxf(m, s_cur[0][r]);
-      }
-      return xor32_max(m) * c;
-    };
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb) s_next[mb] = f32x16{};
-    bf16x8 ka[4];
+    if constexpr (D == 64) set_prio(partner);
+    bf16x8 ka[4], va[3];
+    if constexpr (PV > 0) {
+      va[0] = v_operand(0);
+      va[1] = v_operand(1);
+    } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) ka[i] = k_operand(i);
+      for (int i = 0; i < 4; ++i) ka[i] = k_operand(i);
+    }
     __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      if (i == NS / 2) {
+        issue_loads();
+        if constexpr (D == 64) set_prio(!partner);
+      }
+      if (i < PV) {
+        const int s2 = i / DB;
+        const u32x4 pwv = {p_prev[s2][0], p_prev[s2][1], p_prev[s2][2], p_prev[s2][3]};
+        o[i % DB] =
+            __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i % 3], __builtin_bit_cast(bf16x8, pwv), o[i % DB], 0, 0, 0);
+        if (i + 2 < PV) va[(i + 2) % 3] = v_operand(i + 2);
+      } else {
+        const int q = i - PV;
+        s_next[q / KS] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[q & 3], qreg[q % KS], s_next[q / KS], 0, 0, 0);
+      }
+      if (PV > 0 && i - PV + 4 >= 0 && i - PV + 4 < 4) ka[i - PV + 4] = k_operand(i - PV + 4);
+      if (i >= PV && i - PV + 4 < NQK) ka[(i - PV) & 3] = k_operand(i - PV + 4);
+#pragma unroll
+      for (int k = i * 18 / NS; k < (i + 1) * 18 / NS; ++k) pipe_step(k);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     // Probabilities against the running max: a lane's partial row sum bounds each of its
     // terms, so a sum within PBOUND (NaN and inf fail the test) proves that none exceeds
     // it and the running max may stay; otherwise a cold path moves the max.
-#pragma unroll
-    for (int i = 0; i < NQK; ++i) {
-      s_next[i / KS] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i & 3], qreg[i % KS], s_next[i / KS], 0, 0, 0);
-      if (i + 4 < NQK) ka[i & 3] = k_operand(i + 4);
-      if (i < 12) pipe_slot(i, 0, 10);  // pairs 0..9: P blocks 0, 1 and half of block 2
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int k = NQK; k < 12; ++k) pipe_slot(k, 0, 10);  // head_dim 64: fewer MFMAs than slots
     if (__any(!(rs_a + rs_b <= PBOUND))) {
       // Rare (always at a workgroup's first tile): move the max to the tile's row max
-      // (nothing of this tile is in O^T yet) and form pairs 0..9 again.
-      m_new = fmaxf(tile_max(0), m_run);
+      // (nothing of this tile is in O^T yet) and form the probabilities again.
+      float mx = s_cur[1][0];
+      pin(mx);  // keeps the reduction in the cold path (it was otherwise begun in the hot block)
+#pragma unroll
+      for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s_cur[1][r]);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s_cur[0][r]);
+      m_new = fmaxf(xor32_max(mx) * c, m_run);
       const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
       l_run *= alpha;
       lo_run *= alpha;
 #pragma unroll
       for (int i = 0; i < DB; ++i) o[i] *= alpha;
       m_run = m_new;
-      rs_a = rs_b = 0.f;
 #pragma unroll
-      for (int q = 0; q < 10; ++q) prob_pair(q);
-    }
-
-    // ---- phase B: O^T += V_j^T P_j^T, P block-major; the probabilities of P blocks
-    // 2 and 3 are formed under the MFMAs of blocks 0 and 1. V^T operands come from
-    // LDS transpose reads issued two MFMAs ahead.
-    if (partner) __builtin_amdgcn_s_setprio(0); else __builtin_amdgcn_s_setprio(1);
-    // The next tiles' direct loads: issued here rather than at the top of the iteration, so
-    // their LDS writes do not land under phase A's K operand reads (about -1.5%).
-    if (kc.t < j1) {
-      if (kc.t == n_rt) {
-        cursor_view(std::true_type{}, kc, kc.t);
-      } else if constexpr (SEG) {
-        if (kc.t == kc_end) cursor_next_seg(std::true_type{}, kc);
-      }
-      kc.load(kb_cur, wave_u);
-    }
-    if (vc.t < j1) {
-      if (vc.t == n_rt) {
-        cursor_view(std::false_type{}, vc, vc.t);
-      } else if constexpr (SEG) {
-        if (vc.t == vc_end) cursor_next_seg(std::false_type{}, vc);
-      }
-      vc.load(vb_next, wave_u);
-    }
-    const uint16_t* vs = vb_cur;
-    auto v_operand = [&](int i) {  // i = DB * s2 + db
-      const uint16_t* a = vs + v_lane + 512 * i;
-      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(a));
-      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(a + 128));
-      return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    };
-    bf16x8 va[3];
-    va[0] = v_operand(0);
-    va[1] = v_operand(1);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < NPV; ++i) {
-      const int s2 = i / DB;
-      const u32x4 pwv = {pw[s2][0], pw[s2][1], pw[s2][2], pw[s2][3]};
-      o[i % DB] =
-          __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i % 3], __builtin_bit_cast(bf16x8, pwv), o[i % DB], 0, 0, 0);
-      if (i + 2 < NPV) va[(i + 2) % 3] = v_operand(i + 2);
-      // pairs 10..15 complete P blocks 2 and 3 before the first MFMA that reads them
-      if (DB == 4 && i < 8) pipe_slot(10 + i, 10, 16);
-      if (DB == 2 && i < 3) {
-        prob_pair(10 + 2 * i);
-        prob_pair(11 + 2 * i);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      if (i == 2 * DB - 1 && __any(!(rs_b <= PBOUND))) {
-        // Rare: pairs 8..15 exceed the bound. O^T holds this tile's P blocks 0 and 1
-        // against the old max: rescale it with l and their sum, then form P blocks 2
-        // and 3 against the new max before their MFMAs. Blocks 0 and 1 passed the first
-        // test and only shrink, so the max of key block 1 suffices.
-        m_new = fmaxf(tile_max(1), m_run);
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-        l_run *= alpha;
-        lo_run *= alpha;
-        a01 = alpha;
-        rs_a *= alpha;
-#pragma unroll
-        for (int k = 0; k < DB; ++k) o[k] *= alpha;
-        m_run = m_new;
-        rs_b = 0.f;
-#pragma unroll
-        for (int q = 8; q < 16; ++q) prob_pair(q);
+      for (int q = 0; q < 16; ++q) {
+        const int mb = q >> 3, o2 = (2 * q) & 15;
+        const float e0 = __builtin_amdgcn_exp2f(fmaf(s_cur[mb][o2], c, -m_new));
+        const float e1 = __builtin_amdgcn_exp2f(fmaf(s_cur[mb][o2 + 1], c, -m_new));
+        row_add(q, e0, e1);
+        pack(q, e0, e1);
       }
     }
     l_run += rs_a + rs_b;
@@ -699,10 +597,10 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnParams p) {
       float s01 = 0.f, s23 = 0.f;
 #pragma unroll
       for (int wd = 0; wd < 8; ++wd) {
-        s01 = add_bf16x2(pw[wd >> 2][wd & 3], s01);
-        s23 = add_bf16x2(pw[2 + (wd >> 2)][wd & 3], s23);
+        s01 = add_bf16x2(p_cur[wd >> 2][wd & 3], s01);
+        s23 = add_bf16x2(p_cur[2 + (wd >> 2)][wd & 3], s23);
       }
-      lo_run += s01 * a01 + s23;
+      lo_run += s01 + s23;
       pin(lo_run);
     }
 
@@ -715,13 +613,36 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnParams p) {
     }
     __syncthreads();
   };
+  // O += V_j^T P_j^T of the last tile (in LDS buffer jbc), whose probabilities no iteration follows.
+  auto last_pv = [&](auto jbc, uint32_t(&pl)[4][4]) __attribute__((always_inline)) {
+    const uint16_t* vs = decltype(jbc)::value ? vbuf1 : vbuf0;
+#pragma unroll
+    for (int i = 0; i < NPV; ++i) {
+      const int s2 = i / DB;
+      const uint16_t* a = vs + v_lane + 512 * i;
+      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(a));
+      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(a + 128));
+      const bf16x8 va = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      const u32x4 pwv = {pl[s2][0], pl[s2][1], pl[s2][2], pl[s2][3]};
+      o[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, __builtin_bit_cast(bf16x8, pwv), o[i % DB], 0, 0, 0);
+    }
+  };
 
-  int j = j0;
+  uint32_t pa[4][4], pb[4][4];
+  constexpr std::integral_constant<int, 0> buf0{};
+  constexpr std::integral_constant<int, 1> buf1{};
+  iteration(buf0, std::true_type{}, j0, sa, sb, pb, pa);
+  int j = j0 + 1;
   for (; j + 1 < j1; j += 2) {
-    iteration(std::integral_constant<int, 0>{}, j, sa, sb);
-    iteration(std::integral_constant<int, 1>{}, j + 1, sb, sa);
+    iteration(buf1, std::false_type{}, j, sb, sa, pa, pb);
+    iteration(buf0, std::false_type{}, j + 1, sa, sb, pb, pa);
   }
-  if (j < j1) iteration(std::integral_constant<int, 0>{}, j, sa, sb);
+  if (j < j1) {
+    iteration(buf1, std::false_type{}, j, sb, sa, pa, pb);
+    last_pv(buf1, pb);
+  } else {
+    last_pv(buf0, pa);
+  }
   if (j1 < n_rt) {  // a key chunk inside the reference segment: all of it is reference mass
     if (SEGM) {
       // The chunk ends inside a segment unless its end is a segment end: close its part.
