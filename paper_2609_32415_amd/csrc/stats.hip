@@ -44,6 +44,7 @@ __global__ __launch_bounds__(QF_THREADS) void q_change_final(const float2* ws, i
   if ((int)threadIdx.x >= nh) return;
   const float2* r = s_part + threadIdx.x * (chunks + 1);
   double a = 0.0, c = 0.0;
+#pragma unroll 8
   for (int i = 0; i < chunks; ++i) {
     a += r[i].x;
     c += r[i].y;
@@ -82,6 +83,7 @@ __device__ void gate_decide(int32_t BH, int32_t block, int32_t step, int32_t mod
     s.step = step;
   }
   double sd = 0.0, sm = 0.0, sg = 0.0;
+#pragma unroll 8
   for (int i = 0; i < BH; ++i) {
     const double di = d[i], mi = m[i];
     sd += di;
@@ -227,6 +229,7 @@ __global__ __launch_bounds__(QG_THREADS) void q_change_gate_final(const float4* 
     if ((int)threadIdx.x < nh) {
       const float4* r = s_part + threadIdx.x * (chunks + 1);
       double a = 0.0, c = 0.0, ms = 0.0;
+#pragma unroll 8
       for (int k = 0; k < chunks; ++k) {
         a += r[k].x;
         c += r[k].y;
