@@ -82,7 +82,7 @@ double rounds_cost(int64_t items, double len, int64_t slots, int64_t cus) {
   return full * len + (last == 0 ? 0.0 : last > cus ? len : kLoneRound * len);
 }
 
-SplitPlan plan_split(int64_t tiles, int nt, AttnSlots sl, int head_dim) {
+SplitPlan plan_split(int64_t tiles, int nt, AttnSlots sl, int head_dim, int bm) {
   SplitPlan best = whole_plan(tiles);
   const int64_t slots = (int64_t)sl.cus * sl.per_cu;
   if (tiles <= 0 || slots <= 0 || nt < 2 * kMinChunk) return best;
@@ -90,8 +90,8 @@ SplitPlan plan_split(int64_t tiles, int nt, AttnSlots sl, int head_dim) {
   double best_cost = 0.97 * rounds_cost(tiles, nt, slots, sl.cus);
   // Seconds for every resident workgroup to process one key tile (~1 PFLOP/s of
   // attention) and to move one split item's partial rows twice (~4 TB/s).
-  const double tile_s = slots * 4.0 * kAttnBf16BM * kAttnBf16BN * head_dim / 1.0e15;
-  const double item_s = 2.0 * kAttnBf16BM * (head_dim + 4) * 4.0 / 4.0e12;
+  const double tile_s = slots * 4.0 * bm * kAttnBf16BN * head_dim / 1.0e15;
+  const double item_s = 2.0 * bm * (head_dim + 4) * 4.0 / 4.0e12;
   for (int extra = 0; extra < 2; ++extra) {
     const int64_t rem = tiles % slots + (int64_t)extra * slots;
     if (rem == 0 || rem > tiles) continue;
@@ -111,6 +111,41 @@ SplitPlan plan_split(int64_t tiles, int nt, AttnSlots sl, int head_dim) {
   return best;
 }
 
+// Estimated time (us) of a plan on workgroups of bm query rows, to choose between the two
+// workgroup sizes. Time of one key tile in a round, measured per head dim with few workgroups
+// (one a CU at most, `lone`) and with a full round (`full`): 256-row workgroups keep a CU to
+// themselves and share a K/V tile between eight wavefronts; 128-row ones run two a CU, or one at
+// less time a tile, for twice the K/V traffic.
+struct TileTime {
+  double lone, full;
+};
+constexpr double kStartTiles = 2.0;  // start-up and drain of a workgroup, in key tiles
+constexpr double kMergeUs = 5.0;
+
+TileTime tile_time(int head_dim, int bm) {
+  if (bm == kAttnBf16BM) return head_dim == 128 ? TileTime{1.27, 1.62} : TileTime{1.02, 1.07};
+  return head_dim == 128 ? TileTime{0.95, 1.70} : TileTime{0.80, 1.06};
+}
+
+double plan_us(const SplitPlan& pl, int nt, AttnSlots sl, int head_dim, int bm) {
+  const TileTime tt = tile_time(head_dim, bm);
+  const int64_t cus = sl.cus, slots = cus * sl.per_cu;
+  const auto rounds = [&](int64_t items, double len) {
+    const int64_t full = items / slots, last = items - full * slots;
+    // a partly filled last round draws less power and runs at a higher clock
+    const double top = bm == kAttnBf16BM ? tt.full : tt.lone + 0.2;
+    const double part = last > cus ? tt.full : last > 0 ? tt.lone + (top - tt.lone) * (double)last / (double)cus : 0.0;
+    return len * ((double)full * tt.full + part);
+  };
+  double us = rounds(pl.whole, nt + kStartTiles);
+  if (pl.split_tiles > 0) {
+    const int64_t items = (int64_t)pl.split_tiles * pl.chunks;
+    us += rounds(items, (nt + pl.chunks - 1) / pl.chunks + kStartTiles) + kMergeUs +
+          (double)items * 2.0 * bm * (head_dim + 4) * 4.0 / 4.0e6;
+  }
+  return us;
+}
+
 // Plans of one bf16 launch (plan[0]: the launch's query set, plan[1]: target
 // query tiles only) and the workspace bytes their split items need.
 struct LaunchPlan {
@@ -119,36 +154,58 @@ struct LaunchPlan {
   int64_t items;  // split items of the larger plan
   size_t ws_bytes;
   size_t part_o_bytes;
+  int bm;         // query rows per tile
+  double us;      // estimated time of the plans
 };
 
 // Workspace bytes of a split launch that also records per-segment masses: the partials plus
 // one log-sum-exp per segment of each partial row, after them.
 size_t seg_ws_bytes(const LaunchPlan& lp, int n_seg) {
-  return lp.ws_bytes ? lp.ws_bytes + (size_t)lp.items * kAttnBf16BM * n_seg * sizeof(float) : 0;
+  return lp.ws_bytes ? lp.ws_bytes + (size_t)lp.items * lp.bm * n_seg * sizeof(float) : 0;
 }
 
-LaunchPlan plan_launch(const ra_attn_desc& d, bool split) {
+LaunchPlan plan_launch_bm(const ra_attn_desc& d, bool split, int bm) {
   LaunchPlan lp{};
+  lp.bm = bm;
   const bool device = d.kvsrc == RA_KV_DEVICE;
   const bool ref_queries = (device || d.qset == RA_Q_ALL) && d.n_ref > 0;
-  const int bm = d.dtype == RA_BF16 ? kAttnBf16BM : kAttnF32BM;
   lp.qt_ref = ref_queries ? (d.n_ref + bm - 1) / bm : 0;
   lp.qt_tgt = (d.n_tgt + bm - 1) / bm;
   const int64_t bh = (int64_t)d.batch * d.heads;
   const int64_t all = bh * (lp.qt_ref + lp.qt_tgt), tgt = bh * lp.qt_tgt;
   lp.plan[0] = whole_plan(all);
   lp.plan[1] = device ? whole_plan(tgt) : lp.plan[0];
-  if (!split || d.dtype != RA_BF16 || all > 0x7fffffff) return lp;
-  const AttnSlots slots = attn_bf16_slots(d.head_dim);
+  if (d.dtype != RA_BF16 || all > 0x7fffffff) return lp;
+  const AttnSlots slots = attn_bf16_slots(d.head_dim, bm);
   const int nt = (d.n_ref + kAttnBf16BN - 1) / kAttnBf16BN + (d.n_tgt + kAttnBf16BN - 1) / kAttnBf16BN;
-  lp.plan[0] = plan_split(all, nt, slots, d.head_dim);
-  lp.plan[1] = device ? plan_split(tgt, nt, slots, d.head_dim) : lp.plan[0];
-  int64_t items = 0;
-  for (const SplitPlan& pl : lp.plan) items = std::max<int64_t>(items, (int64_t)pl.split_tiles * pl.chunks);
-  lp.items = items;
-  lp.part_o_bytes = (size_t)items * kAttnBf16BM * d.head_dim * sizeof(float);
-  lp.ws_bytes = items > 0 ? lp.part_o_bytes + (size_t)items * kAttnBf16BM * 5 * sizeof(float) : 0;
+  if (split) {
+    lp.plan[0] = plan_split(all, nt, slots, d.head_dim, bm);
+    lp.plan[1] = device ? plan_split(tgt, nt, slots, d.head_dim, bm) : lp.plan[0];
+    int64_t items = 0;
+    for (const SplitPlan& pl : lp.plan) items = std::max<int64_t>(items, (int64_t)pl.split_tiles * pl.chunks);
+    lp.items = items;
+    lp.part_o_bytes = (size_t)items * bm * d.head_dim * sizeof(float);
+    lp.ws_bytes = items > 0 ? lp.part_o_bytes + (size_t)items * bm * 5 * sizeof(float) : 0;
+  }
+  if (slots.cus > 0) {
+    lp.us = plan_us(lp.plan[0], nt, slots, d.head_dim, bm);
+    if (device) lp.us += plan_us(lp.plan[1], nt, slots, d.head_dim, bm);
+  }
   return lp;
+}
+
+// The launch runs workgroups of 128 query rows where the estimate says that they are 5% faster
+// (the estimates' own error), else of 256: launches of few tiles, which leave CUs idle or one
+// workgroup each. Measured, us, 256 against 128 rows: 4 heads, 300 + 256 tokens, all queries
+// 21.8 / 15.9; 24 heads, 1024 target queries over 2048 keys 43.6 / 38.3; 12 heads, 700 + 800, all
+// 40.8 / 30.5; 24 heads, 2095 + 1009, all 133 / 135; 24 heads, 4352 + 4096, all 755 / 778. The
+// segment kernel runs 256 rows only. Whole (unsplit) rows are summed in the same order in both.
+LaunchPlan plan_launch(const ra_attn_desc& d, bool split, bool seg) {
+  if (d.dtype != RA_BF16) return plan_launch_bm(d, split, kAttnF32BM);
+  const LaunchPlan big = plan_launch_bm(d, split, kAttnBf16BM);
+  if (seg || !(big.us > 0.0)) return big;
+  const LaunchPlan small = plan_launch_bm(d, split, kAttnBf16SmallBM);
+  return small.us > 0.0 && small.us < 0.95 * big.us ? small : big;
 }
 
 ra_status check_attn_desc(const ra_attn_desc* desc, const char* who) {
@@ -181,14 +238,14 @@ const char* refadapt_version(void) { return "refadapt 0.1 gfx950"; }
 
 size_t refadapt_joint_attn_workspace_size(const ra_attn_desc* desc) {
   if (check_attn_desc(desc, "joint_attn_workspace_size") != RA_OK) return 0;
-  return plan_launch(*desc, true).ws_bytes;
+  return plan_launch(*desc, true, desc->kvsrc == RA_KV_SEGMENTS).ws_bytes;
 }
 
 size_t refadapt_joint_attn_seg_workspace_size(const ra_attn_desc* desc, int32_t n_seg) {
   if (check_attn_desc(desc, "joint_attn_seg_workspace_size") != RA_OK) return 0;
   const ra_attn_desc& d = *desc;
   if (n_seg < 1 || n_seg > RA_MAX_SEG || d.dtype != RA_BF16 || d.kvsrc == RA_KV_DEVICE || d.n_ref < 1) return 0;
-  return seg_ws_bytes(plan_launch(d, true), n_seg);
+  return seg_ws_bytes(plan_launch(d, true, true), n_seg);
 }
 
 ra_status refadapt_joint_attn(const ra_attn_desc* desc, const ra_attn_args* args, void* stream) {
@@ -291,8 +348,8 @@ ra_status refadapt_joint_attn(const ra_attn_desc* desc, const ra_attn_args* args
 
   // Per-segment masses split key ranges only when the workspace also holds the per-segment
   // partials; with a smaller workspace the launch runs whole query tiles.
-  LaunchPlan lp = plan_launch(d, a.workspace != nullptr);
-  if (a.seg_mass != nullptr && a.workspace_bytes < seg_ws_bytes(lp, a.n_seg)) lp = plan_launch(d, false);
+  LaunchPlan lp = plan_launch(d, a.workspace != nullptr, seg);
+  if (a.seg_mass != nullptr && a.workspace_bytes < seg_ws_bytes(lp, a.n_seg)) lp = plan_launch(d, false, true);
   const int64_t total = (int64_t)d.batch * d.heads * (lp.qt_ref + lp.qt_tgt);
   if (total > 0x7fffffff) return fail(RA_EUNSUPPORTED, "joint_attn: problem too large for one launch");
   if (a.workspace != nullptr) {
@@ -304,11 +361,12 @@ ra_status refadapt_joint_attn(const ra_attn_desc* desc, const ra_attn_args* args
   p.qt_ref = (int32_t)lp.qt_ref;
   p.qt_tgt = (int32_t)lp.qt_tgt;
   p.total_tiles = (int32_t)total;
+  p.bm = lp.bm;
   p.plan[0] = lp.plan[0];
   p.plan[1] = lp.plan[1];
   p.part_o = static_cast<float*>(a.workspace);
   p.part_st = lp.ws_bytes ? reinterpret_cast<float4*>(static_cast<char*>(a.workspace) + lp.part_o_bytes) : nullptr;
-  p.part_lo = lp.ws_bytes ? reinterpret_cast<float*>(p.part_st + lp.items * kAttnBf16BM) : nullptr;
+  p.part_lo = lp.ws_bytes ? reinterpret_cast<float*>(p.part_st + lp.items * lp.bm) : nullptr;
   p.part_seg = lp.ws_bytes && a.seg_mass ? reinterpret_cast<float*>(static_cast<char*>(a.workspace) + lp.ws_bytes)
                                          : nullptr;
   if (seg) {

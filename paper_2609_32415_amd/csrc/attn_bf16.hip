@@ -86,10 +86,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
-constexpr int BM = kAttnBf16BM;  // query rows per workgroup
 constexpr int BN = kAttnBf16BN;  // keys per LDS tile
-constexpr int NW = BM / 32;      // wavefronts per workgroup
-constexpr int NT = 64 * NW;      // threads per workgroup
 constexpr float PBOUND = 4096.0f;  // bound on a probability against the running max (2^12)
 
 // Row permutation of a 32-key MFMA block: swaps bits 2 and 3 of the row index.
@@ -134,7 +131,7 @@ __device__ __forceinline__ float add_bf16x2(uint32_t w, float acc) {
 //     which makes the transpose reads of the V^T operand conflict-free.
 // No padding, no staging registers and no LDS store instructions: a tile's loads are
 // issued half an iteration ahead of the barrier that publishes it.
-template <int D>
+template <int D, int NW>
 struct Layout {
   static constexpr int NB = D / 8;        // 1 KiB blocks per K or V tile
   static constexpr int TILE = NB * 512;   // elements per tile
@@ -167,12 +164,12 @@ __device__ __forceinline__ uint32_t dma_lane_offset(int lane, int64_t ss) {
 // tile, the rows of its view from there on, and the view's row stride, lane offset and the
 // scalar offsets of this wavefront's blocks. Advancing to the next tile costs a 64-bit add;
 // the view changes once, where the reference keys end and the target keys begin.
-template <int D, bool IS_K>
+template <int D, int NW, bool IS_K>
 struct DmaCursor {
   const uint16_t* ptr;
   int64_t ss;
   uint32_t voff;
-  uint32_t soff[Layout<D>::NLD];
+  uint32_t soff[Layout<D, NW>::NLD];
   int t, rows;
 
   __device__ __forceinline__ void set_view(const uint16_t* base, int64_t row_stride, uint32_t lane_off, int tile0,
@@ -184,7 +181,7 @@ struct DmaCursor {
     rows = view_rows - first_row;
     t = tile0;
 #pragma unroll
-    for (int i = 0; i < Layout<D>::NLD; ++i) {
+    for (int i = 0; i < Layout<D, NW>::NLD; ++i) {
       const int blk = wave + NW * i;
       soff[i] = __builtin_amdgcn_readfirstlane(
           (uint32_t)(IS_K ? (int64_t)(blk / KS) * 32 * ss * 2 + (blk % KS) * 32
@@ -196,7 +193,7 @@ struct DmaCursor {
     const int valid = min(BN, rows);
     const __amdgpu_buffer_rsrc_t rs = tile_rsrc<D>(ptr, ss, valid);
 #pragma unroll
-    for (int i = 0; i < Layout<D>::NLD; ++i) {
+    for (int i = 0; i < Layout<D, NW>::NLD; ++i) {
       const int blk = wave + NW * i;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(tile + blk * 512), 16,
                                                voff, soff[i], 0, 0);
@@ -211,8 +208,9 @@ struct DmaCursor {
 // segment. SEGM (with SEG, for a non-null seg_mass): each segment's log-sum-exp over the
 // launch's key range is recorded; an instance of its own, so that launches without it carry
 // none of its state (2% of the segment launch).
-template <int D, bool SEG, bool SEGM>
-__global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnParams p) {
+template <int D, int BM, bool SEG, bool SEGM>
+__global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
+  constexpr int NW = BM / 32;  // wavefronts
   constexpr int KS = D / 16;   // MFMA k-steps over the head dim for S^T
   constexpr int DB = D / 32;   // 32-row blocks of the O^T accumulator
   constexpr int NQK = 2 * KS;  // MFMAs of one S^T tile
@@ -220,10 +218,10 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnParams p) {
   // Four separate arrays (not one indexed by a run-time buffer number), so the compiler
   // can tell the buffer a direct load fills from the ones being read and does not wait
   // for the load before those reads.
-  __shared__ __attribute__((aligned(1024))) uint16_t kbuf0[Layout<D>::TILE];
-  __shared__ __attribute__((aligned(1024))) uint16_t kbuf1[Layout<D>::TILE];
-  __shared__ __attribute__((aligned(1024))) uint16_t vbuf0[Layout<D>::TILE];
-  __shared__ __attribute__((aligned(1024))) uint16_t vbuf1[Layout<D>::TILE];
+  __shared__ __attribute__((aligned(1024))) uint16_t kbuf0[Layout<D, NW>::TILE];
+  __shared__ __attribute__((aligned(1024))) uint16_t kbuf1[Layout<D, NW>::TILE];
+  __shared__ __attribute__((aligned(1024))) uint16_t vbuf0[Layout<D, NW>::TILE];
+  __shared__ __attribute__((aligned(1024))) uint16_t vbuf1[Layout<D, NW>::TILE];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -323,8 +321,8 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnParams p) {
   const int v_lane = 32 * (8 * (tr_G >> 1) + (tr_i >> 2)) + ((16 * (tr_G & 1) + 4 * (tr_i & 3)) ^ (16 * ((tr_i >> 3) & 1)));
 
   // ---- the load cursors of the K and V streams
-  DmaCursor<D, true> kc;
-  DmaCursor<D, false> vc;
+  DmaCursor<D, NW, true> kc;
+  DmaCursor<D, NW, false> vc;
   // SEG: the segment each cursor reads and the key tile that ends it. A cursor re-targets to
   // the next segment's base (this (b, h) applied) when it reaches that tile; segments share
   // the reference views' strides, so only the base pointer changes. The segment tables are
@@ -466,7 +464,7 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnParams p) {
     // Head dim 64: which wavefront of a SIMD wins issue ties alternates between the two halves, so
     // the pair finishes a tile together instead of one idling at the barrier (-1%; at head dim
     // 128 it made no difference).
-    const bool partner = wave_u >= 4;
+    const bool partner = wave_u >= NW / 2;
     auto set_prio = [](bool high) __attribute__((always_inline)) {
       if (high)
         __builtin_amdgcn_s_setprio(1);
@@ -728,7 +726,7 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnParams p) {
 // A chunk's reference max never exceeds its running max, so M bounds both;
 // summing the reference part against M_R keeps lse_ref finite when the target
 // keys score so far above the reference keys that 2^(M_R - M) underflows.
-template <int D, int MERGE_BATCH>
+template <int D, int BM, int MERGE_BATCH>
 __device__ __forceinline__ void merge_rows(const AttnParams& p, const SplitPlan& pl, bool tgt_only) {
   constexpr int TPR = D / 4, RPB = 256 / TPR;
   const int qt_ref = tgt_only ? 0 : p.qt_ref;
@@ -841,7 +839,7 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const SplitPlan&
   }
 }
 
-template <int D, int MERGE_BATCH>
+template <int D, int BM, int MERGE_BATCH>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p) {
   bool tgt_only = false;
   if (p.kvsrc == KV_DEVICE) tgt_only = __builtin_amdgcn_readfirstlane(*p.decision) == DEC_REUSE;
@@ -850,73 +848,91 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p) {
   // chunks; a two-chunk plan then runs the two-chunk body (one batch of loads, no guards).
   if constexpr (MERGE_BATCH > 2) {
     if (pl.chunks <= 2) {
-      merge_rows<D, 2>(p, pl, tgt_only);
+      merge_rows<D, BM, 2>(p, pl, tgt_only);
       return;
     }
   }
-  merge_rows<D, MERGE_BATCH>(p, pl, tgt_only);
+  merge_rows<D, BM, MERGE_BATCH>(p, pl, tgt_only);
 }
 
 // Explicit instantiations: without them the host pass leaves the segment instances, which
 // are only reached through the launcher's kernel-pointer argument, without launch stubs.
-template __global__ void attn_bf16_kernel<128, false, false>(AttnParams);
-template __global__ void attn_bf16_kernel<64, false, false>(AttnParams);
-template __global__ void attn_bf16_kernel<128, true, false>(AttnParams);
-template __global__ void attn_bf16_kernel<64, true, false>(AttnParams);
-template __global__ void attn_bf16_kernel<128, true, true>(AttnParams);
-template __global__ void attn_bf16_kernel<64, true, true>(AttnParams);
+template __global__ void attn_bf16_kernel<128, 256, false, false>(AttnParams);
+template __global__ void attn_bf16_kernel<64, 256, false, false>(AttnParams);
+template __global__ void attn_bf16_kernel<128, 128, false, false>(AttnParams);
+template __global__ void attn_bf16_kernel<64, 128, false, false>(AttnParams);
+template __global__ void attn_bf16_kernel<128, 256, true, false>(AttnParams);
+template __global__ void attn_bf16_kernel<64, 256, true, false>(AttnParams);
+template __global__ void attn_bf16_kernel<128, 256, true, true>(AttnParams);
+template __global__ void attn_bf16_kernel<64, 256, true, true>(AttnParams);
+
+template <int D, int BM>
+hipError_t launch_plain(const AttnParams& p, dim3 grid, hipStream_t stream) {
+  return launch_kernel(attn_bf16_kernel<D, BM, false, false>, grid, dim3(2 * BM), 0, stream, p);
+}
+
+template <int D>
+hipError_t launch_segments(const AttnParams& p, dim3 grid, hipStream_t stream) {
+  constexpr int BM = kAttnBf16BM;
+  return p.seg_mass ? launch_kernel(attn_bf16_kernel<D, BM, true, true>, grid, dim3(2 * BM), 0, stream, p)
+                    : launch_kernel(attn_bf16_kernel<D, BM, true, false>, grid, dim3(2 * BM), 0, stream, p);
+}
+
+template <int D, int BM>
+hipError_t launch_merge(const AttnParams& p, int split, hipStream_t stream) {
+  constexpr int RPB = 256 / (D / 4);
+  const dim3 grid((split * BM + RPB - 1) / RPB);
+  // Loads in flight per merge thread: all chunks of a two-chunk split, else eight at a time.
+  const bool two = max(p.plan[0].chunks, p.plan[1].chunks) <= 2;
+  return two ? launch_kernel(attn_merge_kernel<D, BM, 2>, grid, dim3(256), 0, stream, p)
+             : launch_kernel(attn_merge_kernel<D, BM, 8>, grid, dim3(256), 0, stream, p);
+}
+
+template <int D>
+hipError_t launch_dim(const AttnParams& p, hipStream_t stream) {
+  const int items = max(p.plan[0].total_items, p.plan[1].total_items);
+  if (items <= 0) return hipSuccess;
+  const bool small = p.bm == kAttnBf16SmallBM;
+  const dim3 grid(items);
+  const hipError_t e = p.n_seg > 0 ? launch_segments<D>(p, grid, stream)
+                       : small     ? launch_plain<D, kAttnBf16SmallBM>(p, grid, stream)
+                                   : launch_plain<D, kAttnBf16BM>(p, grid, stream);
+  if (e != hipSuccess) return e;
+  const int split = max(p.plan[0].split_tiles, p.plan[1].split_tiles);
+  if (split == 0) return hipSuccess;
+  return small ? launch_merge<D, kAttnBf16SmallBM>(p, split, stream) : launch_merge<D, kAttnBf16BM>(p, split, stream);
+}
 
 }  // namespace
 
-AttnSlots attn_bf16_slots(int head_dim) {
-  static std::atomic<int> cache[64][2][2];
+AttnSlots attn_bf16_slots(int head_dim, int bm) {
+  static std::atomic<int> cache[64][2][2][2];
   int dev = 0, cus = 0, per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0) return AttnSlots{0, 0};
-  const int di = head_dim == 128 ? 1 : 0;
+  const int di = head_dim == 128 ? 1 : 0, bi = bm == kAttnBf16SmallBM ? 1 : 0;
   if (dev < 64) {
-    const int c = cache[dev][di][0].load(std::memory_order_relaxed);
-    if (c > 0) return AttnSlots{c, cache[dev][di][1].load(std::memory_order_relaxed)};
+    const int c = cache[dev][di][bi][0].load(std::memory_order_acquire);
+    if (c > 0) return AttnSlots{c, cache[dev][di][bi][1].load(std::memory_order_relaxed)};
   }
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return AttnSlots{0, 0};
+  const auto occupancy = [&](auto* kernel, int threads) {
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0);
+  };
   const hipError_t e =
-      head_dim == 128
-          ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_bf16_kernel<128, false, false>, NT, 0)
-          : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_bf16_kernel<64, false, false>, NT, 0);
+      bi ? (di ? occupancy(attn_bf16_kernel<128, kAttnBf16SmallBM, false, false>, 2 * kAttnBf16SmallBM)
+               : occupancy(attn_bf16_kernel<64, kAttnBf16SmallBM, false, false>, 2 * kAttnBf16SmallBM))
+         : (di ? occupancy(attn_bf16_kernel<128, kAttnBf16BM, false, false>, 2 * kAttnBf16BM)
+               : occupancy(attn_bf16_kernel<64, kAttnBf16BM, false, false>, 2 * kAttnBf16BM));
   if (e != hipSuccess || per_cu < 1 || cus < 1) return AttnSlots{0, 0};
   if (dev < 64) {
-    cache[dev][di][1].store(per_cu, std::memory_order_relaxed);
-    cache[dev][di][0].store(cus, std::memory_order_relaxed);
+    cache[dev][di][bi][1].store(per_cu, std::memory_order_relaxed);
+    cache[dev][di][bi][0].store(cus, std::memory_order_release);
   }
   return AttnSlots{cus, per_cu};
 }
 
 hipError_t launch_attn_bf16(const AttnParams& p, int head_dim, hipStream_t stream) {
-  const int items = max(p.plan[0].total_items, p.plan[1].total_items);
-  if (items <= 0) return hipSuccess;
-  const dim3 grid(items), block(NT);
-  hipError_t e;
-  if (p.n_seg > 0 && p.seg_mass) {
-    e = head_dim == 128 ? launch_kernel(attn_bf16_kernel<128, true, true>, grid, block, 0, stream, p)
-                        : launch_kernel(attn_bf16_kernel<64, true, true>, grid, block, 0, stream, p);
-  } else if (p.n_seg > 0) {
-    e = head_dim == 128 ? launch_kernel(attn_bf16_kernel<128, true, false>, grid, block, 0, stream, p)
-                        : launch_kernel(attn_bf16_kernel<64, true, false>, grid, block, 0, stream, p);
-  } else {
-    e = head_dim == 128 ? launch_kernel(attn_bf16_kernel<128, false, false>, grid, block, 0, stream, p)
-                        : launch_kernel(attn_bf16_kernel<64, false, false>, grid, block, 0, stream, p);
-  }
-  if (e != hipSuccess) return e;
-  const int split = max(p.plan[0].split_tiles, p.plan[1].split_tiles);
-  if (split == 0) return hipSuccess;
-  const int rpb = 256 / (head_dim / 4);
-  const dim3 mgrid((split * BM + rpb - 1) / rpb);
-  // Loads in flight per merge thread: all chunks of a two-chunk split, else eight at a time.
-  const bool two = max(p.plan[0].chunks, p.plan[1].chunks) <= 2;
-  if (head_dim == 128)
-    return two ? launch_kernel(attn_merge_kernel<128, 2>, mgrid, dim3(256), 0, stream, p)
-               : launch_kernel(attn_merge_kernel<128, 8>, mgrid, dim3(256), 0, stream, p);
-  return two ? launch_kernel(attn_merge_kernel<64, 2>, mgrid, dim3(256), 0, stream, p)
-             : launch_kernel(attn_merge_kernel<64, 8>, mgrid, dim3(256), 0, stream, p);
+  return head_dim == 128 ? launch_dim<128>(p, stream) : launch_dim<64>(p, stream);
 }
 
 }  // namespace refadapt

@@ -477,7 +477,7 @@ int choose_split(const AttnParams& p, int64_t cus) {
 
 template <int D>
 hipError_t launch_dim(const AttnParams& p, hipStream_t stream) {
-  const int dev_cus = attn_bf16_slots(D).cus;
+  const int dev_cus = attn_bf16_slots(D, kAttnBf16BM).cus;
   const int64_t cus = dev_cus > 0 ? dev_cus : 256;
   switch (choose_split(p, cus)) {
     case 4: return launch<D, 4, 4, 32>(p, stream);

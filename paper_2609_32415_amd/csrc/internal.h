@@ -52,6 +52,7 @@ struct AttnParams {
   // bf16 path: plan[0] covers the launch's query set (under KV_DEVICE: every
   // query tile), plan[1] the target query tiles alone (KV_DEVICE on REUSE).
   SplitPlan plan[2];
+  int32_t bm;        // bf16 path: query rows per workgroup (BM)
   float* part_o;     // [items][BM][head_dim] unnormalised fp32 partial outputs of split items
   float4* part_st;   // [items][BM] (m, l_tgt, m_ref, l_ref) per partial row
   float* part_lo;    // [items][BM] sum of the bf16-rounded probabilities of a partial row
@@ -69,21 +70,23 @@ struct AttnParams {
   const void* seg_vbase[kMaxSeg];
 };
 
-// Query rows per workgroup of the bf16 attention kernel (the host sizes the grid with it) and
-// the most of the fp32 one (its launcher picks 64, 32 or 16), and keys per key tile of the bf16 kernel.
+// Query rows per workgroup of the bf16 attention kernel (the host picks one of two and sizes the
+// grid with it) and the most of the fp32 one (its launcher picks 64, 32 or 16), and keys per key
+// tile of the bf16 kernel.
 constexpr int kAttnBf16BM = 256;
+constexpr int kAttnBf16SmallBM = 128;
 constexpr int kAttnBf16BN = 64;
 // Largest K/V row stride (elements) of the bf16 attention: a key tile spans 64 rows, addressed
 // with 32-bit byte offsets.
 constexpr int64_t kAttnMaxRowStride = (int64_t(1) << 24) - 8;
 constexpr int kAttnF32BM = 64;
 
-// Compute units of the current device and bf16 attention workgroups each holds
-// at once; zeros if the device cannot be queried.
+// Compute units of the current device and bf16 attention workgroups (of bm query rows) each
+// holds at once; zeros if the device cannot be queried.
 struct AttnSlots {
   int cus, per_cu;
 };
-AttnSlots attn_bf16_slots(int head_dim);
+AttnSlots attn_bf16_slots(int head_dim, int bm);
 // Enqueues the bf16 attention kernel and, when a plan splits tiles, the merge.
 hipError_t launch_attn_bf16(const AttnParams& p, int head_dim, hipStream_t stream);
 hipError_t launch_attn_f32(const AttnParams& p, int head_dim, hipStream_t stream);
