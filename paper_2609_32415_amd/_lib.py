@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 
 # torch must be imported before the library is loaded: torch ships its own HIP
 # runtime (SONAME libamdhip64.so.7) and requests it as "libamdhip64.so"; loaded
@@ -187,6 +188,14 @@ def _load():
 
 LIB = _load()
 
+# joint_attn on descriptor and argument blocks packed by struct (one C call each) instead of built
+# field by field as ctypes structures: a call's host time is most of a small launch's.
+DESC_PACK = struct.Struct("=6if2i")  # ra_attn_desc
+ARGS_PACK = struct.Struct("=32qq8q5q18iq4qq")  # ra_attn_args, field by field
+assert DESC_PACK.size == ctypes.sizeof(ra_attn_desc) and ARGS_PACK.size == ctypes.sizeof(ra_attn_args)
+_joint_attn_packed = ctypes.CFUNCTYPE(ctypes.c_int32, ctypes.c_char_p, ctypes.c_char_p, ctypes.c_void_p)(
+    ("refadapt_joint_attn", LIB))
+
 
 def _check(status):
     if status != RA_OK:
@@ -197,6 +206,11 @@ def _check(status):
 def refadapt_joint_attn(desc, args, stream):
     """Forward to ``refadapt_joint_attn``; raises RefadaptError on a non-OK status."""
     return _check(LIB.refadapt_joint_attn(ctypes.byref(desc), ctypes.byref(args), stream))
+
+
+def refadapt_joint_attn_packed(desc, args, stream):
+    """``refadapt_joint_attn`` on bytes of DESC_PACK and ARGS_PACK."""
+    return _check(_joint_attn_packed(desc, args, stream))
 
 
 def refadapt_joint_attn_workspace_size(desc):

@@ -96,15 +96,21 @@ class Controller:
             q_prev = self.q_anchor[b] if t > 0 else x["q_tgt"]
         else:
             q_prev = self.q_prev[b] if self.q_prev[b] is not None else x["q_tgt"]
-        dec = self.decisions[t, b:b + 1]
+        # one view op each (indexing with a slice or a pair of indices takes three times as long)
+        if not 0 <= t < self.decisions.shape[0]:
+            raise IndexError(f"step {t} is outside the trajectory's {self.decisions.shape[0]} steps")
+        cell = t * self.nb + b
+        dec = self.decisions.as_strided((1,), (1,), cell)
+        d, age = self.d.select(0, b), self.age.as_strided((1,), (1,), b)
+        score = self.scores.as_strided((3,), (1,), 3 * cell)
         if self.fused:
             ops.q_change_gate(x["q_tgt"], q_prev, self.mass[b][self.parity[b]], self.theta, self.state, b, t,
-                              self.mode, self.eps, d_out=self.d[b], decision_out=dec, score_out=self.scores[t, b],
+                              self.mode, self.eps, d_out=d, decision_out=dec, score_out=score,
                               workspace=self.ws)
         else:
-            ops.q_change(x["q_tgt"], q_prev, self.eps, out=self.d[b], workspace=self.ws)
-            ops.gate(self.d[b], self.mass[b][self.parity[b]], self.theta, self.state, b, t, self.mode,
-                     decision_out=dec, score_out=self.scores[t, b])
+            ops.q_change(x["q_tgt"], q_prev, self.eps, out=d, workspace=self.ws)
+            ops.gate(d, self.mass[b][self.parity[b]], self.theta, self.state, b, t, self.mode,
+                     decision_out=dec, score_out=score)
         if mark:
             mark("gate")
         nxt = 1 - self.parity[b]
@@ -119,7 +125,7 @@ class Controller:
         if self.sidecar is not None:  # read-only probes; the block's cache still holds its anchor K/V
             self.sidecar.block(t, b, x, self)
         ops.cache_commit(x["k_ref"], x["v_ref"], self.k_cache[b], self.v_cache[b], decision=dec,
-                         age=self.age[b:b + 1], step=t, q_ref=x["q_ref"], q_cache=self.q_cache[b])
+                         age=age, step=t, q_ref=x["q_ref"], q_cache=self.q_cache[b])
         if self.cue == "anchor":
             ops.cache_commit(x["q_tgt"], None, self.q_anchor[b], None, decision=dec)
         if mark:

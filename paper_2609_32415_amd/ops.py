@@ -21,11 +21,18 @@ _QSET = {"target": L.RA_Q_TARGET, "all": L.RA_Q_ALL}
 _KVSRC = {"fresh": L.RA_KV_FRESH, "cache": L.RA_KV_CACHE, "device": L.RA_KV_DEVICE, "segments": L.RA_KV_SEGMENTS}
 _GATE = {"product": L.RA_GATE_PRODUCT, "q_only": L.RA_GATE_Q_ONLY, "mass_only": L.RA_GATE_MASS_ONLY, "and": L.RA_GATE_AND}
 
+_NO_SEGS = (0,) * L.RA_MAX_SEG
+_NO_SEG_FIELDS = (0, *_NO_SEGS, 0)  # n_seg, seg_end, seg_cache
+
 REUSE, REACTIVATE, COMPUTE = L.RA_REUSE, L.RA_REACTIVATE, L.RA_COMPUTE
 
 
+_NO_TENSOR = (0, 0, 0, 0)
+
+
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current stream of the current device, without building a torch.cuda.Stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _on_gpu(name, t):
@@ -33,27 +40,33 @@ def _on_gpu(name, t):
         raise ValueError(f"{name} must be a GPU tensor (the HIP library is the only implementation)")
 
 
-def _view(name, t, dtype=None, shape=None):
+def _quad(name, t, dtype, shape):
+    """(data pointer, batch, head and row strides) of a [B, H, S, d] tensor, checked."""
     if t is None:
-        return L.ra_tensor()
-    _on_gpu(name, t)
-    if t.dim() != 4:
-        raise ValueError(f"{name} must be [B, H, S, d], got {tuple(t.shape)}")
-    if shape is not None and tuple(t.shape) != tuple(shape):
-        raise ValueError(f"{name}: shape {tuple(t.shape)} != {tuple(shape)}")
-    if t.numel() == 0:  # an empty segment is never read: pass a null view
-        return L.ra_tensor()
-    if t.stride(-1) != 1:
+        return _NO_TENSOR
+    if not t.is_cuda:
+        _on_gpu(name, t)
+    sh = t.shape
+    if len(sh) != 4:
+        raise ValueError(f"{name} must be [B, H, S, d], got {tuple(sh)}")
+    if shape is not None and sh != shape:
+        raise ValueError(f"{name}: shape {tuple(sh)} != {tuple(shape)}")
+    if 0 in sh:  # an empty segment is never read: pass a null view
+        return _NO_TENSOR
+    sb, shd, ss, sd = t.stride()
+    if sd != 1:
         raise ValueError(f"{name}: the head dimension must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"{name}: dtype {t.dtype} differs from {dtype}")
-    if shape is not None and tuple(t.shape) != tuple(shape):
-        raise ValueError(f"{name}: shape {tuple(t.shape)} != {tuple(shape)}")
-    return L.ra_tensor(t.data_ptr(), t.stride(0), t.stride(1), t.stride(2))
+    return t.data_ptr(), sb, shd, ss
+
+
+def _view(name, t, dtype=None, shape=None):
+    return L.ra_tensor(*_quad(name, t, dtype, shape))
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _probe_ptr(t):
@@ -165,43 +178,38 @@ def joint_attn(
 
     shp_t = (B, H, n_tgt, D)
     shp_r = (B, H, n_ref, D)
-    desc = L.ra_attn_desc(B, H, D, n_ref, n_tgt, _DTYPES[dt], float(scale or 0.0), _QSET[qset], _KVSRC[kvsrc])
+    desc = (B, H, D, n_ref, n_tgt, _DTYPES[dt],
+            ctypes.c_float(scale).value if scale else 0.0, _QSET[qset], _KVSRC[kvsrc])
     if workspace is None:
         if smass_t is not None:
-            nbytes = L.refadapt_joint_attn_seg_workspace_size(desc, n_seg)
+            nbytes = L.refadapt_joint_attn_seg_workspace_size(L.ra_attn_desc(*desc), n_seg)
         else:
-            nbytes = L.refadapt_joint_attn_workspace_size(desc)
+            nbytes = L.refadapt_joint_attn_workspace_size(L.ra_attn_desc(*desc))
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev) if nbytes else False
     if workspace is False:
-        ws_ptr, ws_bytes = None, 0
+        ws_ptr, ws_bytes = 0, 0
     else:
         _on_gpu("workspace", workspace)
         ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
-    args = L.ra_attn_args(
-        q_tgt=_view("q_tgt", q_tgt, dt, shp_t),
-        k_tgt=_view("k_tgt", k_tgt, dt, shp_t),
-        v_tgt=_view("v_tgt", v_tgt, dt, shp_t),
-        q_ref=_view("q_ref", q_ref, dt, shp_r),
-        k_ref=_view("k_ref", k_ref, dt, shp_r),
-        v_ref=_view("v_ref", v_ref, dt, shp_r),
-        k_cache=_view("k_cache", k_cache, dt, shp_r),
-        v_cache=_view("v_cache", v_cache, dt, shp_r),
-        decision=None if decision is None else decision.data_ptr(),
-        o_tgt=_view("o_tgt", o_tgt, dt, shp_t),
-        o_ref=_view("o_ref", o_ref, dt, shp_r),
-        ref_mass=None if mass_t is None else mass_t.data_ptr(),
-        lse_tgt=None if lse_t is None else lse_t.data_ptr(),
-        ref_mass_refq=None if mrq_t is None else mrq_t.data_ptr(),
-        workspace=ws_ptr,
-        workspace_bytes=ws_bytes,
-        n_seg=n_seg,
-        seg_end=(ctypes.c_int32 * L.RA_MAX_SEG)(*(list(seg_end or []) + [0] * (L.RA_MAX_SEG - n_seg))),
-        seg_cache=cache_bits,
-        seg_mass=None if smass_t is None else smass_t.data_ptr(),
-        q_cache=_view("q_cache", q_cache, dt, shp_r),
-        clock_probe=None if clock_probe is None else _probe_ptr(clock_probe),
+    if n_seg:
+        segs = (n_seg, *seg_end, *_NO_SEGS[n_seg:], cache_bits)
+    else:
+        segs = _NO_SEG_FIELDS
+    args = L.ARGS_PACK.pack(
+        *_quad("q_tgt", q_tgt, dt, shp_t), *_quad("k_tgt", k_tgt, dt, shp_t), *_quad("v_tgt", v_tgt, dt, shp_t),
+        *_quad("q_ref", q_ref, dt, shp_r), *_quad("k_ref", k_ref, dt, shp_r), *_quad("v_ref", v_ref, dt, shp_r),
+        *_quad("k_cache", k_cache, dt, shp_r), *_quad("v_cache", v_cache, dt, shp_r),
+        0 if decision is None else decision.data_ptr(),
+        *_quad("o_tgt", o_tgt, dt, shp_t), *_quad("o_ref", o_ref, dt, shp_r),
+        0 if mass_t is None else mass_t.data_ptr(),
+        0 if lse_t is None else lse_t.data_ptr(),
+        0 if mrq_t is None else mrq_t.data_ptr(),
+        ws_ptr, ws_bytes, *segs,
+        0 if smass_t is None else smass_t.data_ptr(),
+        *_quad("q_cache", q_cache, dt, shp_r),
+        0 if clock_probe is None else _probe_ptr(clock_probe),
     )
-    L.refadapt_joint_attn(desc, args, _stream())
+    L.refadapt_joint_attn_packed(L.DESC_PACK.pack(*desc), args, _stream())
     return AttnOut(o_tgt, o_ref if ref_queries else None, mass_t, lse_t, mrq_t, smass_t)
 
 
@@ -516,7 +524,7 @@ def mfma_rate_probe(kind, operands, steps, workgroups=None, sink=None, clock_pro
     _on_gpu("sink", sink)
     if sink.dtype != torch.float32 or sink.numel() < workgroups * 512:
         raise ValueError("sink must be a float32 tensor of at least workgroups * 512 elements")
-    probe = None if clock_probe is None else _ptr(clock_probe)
+    probe = _ptr(clock_probe)
     L.refadapt_mfma_rate_probe({"dense": L.RA_PROBE_DENSE, "mix": L.RA_PROBE_MIX}[kind], int(workgroups), int(steps),
                                _ptr(operands), _ptr(sink), probe, _stream())
     return sink
