@@ -20,8 +20,8 @@
 // instructions of one step never wait on each other; sched_barrier fences keep that order.
 // Against two phases a tile (S_{j+1} with pairs 0..9, then O += V_j^T P_j^T with the rest, each
 // with its own operand latency and bound test): 2.82 -> 2.75 ms at 24 heads of 128, 16640 queries
-// and keys (1.21 -> 1.24 PFLOP/s; a large library product reaches 1.27), 486 -> 460 us at 24 heads
-// of 64, 8448 queries and keys.
+// and keys, 486 -> 460 us at 24 heads of 64, 8448 queries and keys. With the bare rows below the
+// first runs at 1.26 PFLOP/s; a large library product reaches 1.27 on the same part.
 // K tiles run two tiles ahead of V tiles through two LDS buffers each. Half-way through
 // iteration j direct global-to-LDS loads (no staging registers, no LDS store
 // instructions) fill the buffers that held K_j and V_{j-2} with K_{j+2} and
@@ -42,7 +42,9 @@
 // the scores, rescales O and l, and forms the probabilities again. The
 // O rescale and the row max are thus almost never executed.
 // Row sums add the fp32 probabilities, so the reference mass and the
-// log-sum-exp carry no bf16 rounding. O is divided by a second sum, that of
+// log-sum-exp carry no bf16 rounding. Rows that want neither (the reference rows of most
+// launches) skip them and take the bound test on the rounded sum below: 2.78 -> 2.71 ms at 24
+// heads of 128, 12544 of the 16640 queries bare; 467 -> 455 us at 24 heads of 64, 4352 of 8448. O is divided by a second sum, that of
 // the bf16-rounded probabilities it accumulated (one v_dot2c_f32_bf16 per
 // packed pair, after the tile's last MFMA), so the weights
 // applied to V sum to one: with the fp32 sum, the rounding of a dominant
@@ -110,6 +112,14 @@ __device__ __forceinline__ float xor32_add(float v) {
 template <typename T>
 __device__ __forceinline__ void pin(T& v) {
   asm volatile("" : "+v"(v));
+}
+
+// The lane number, computed here and now: a value kept from before the key loop would hold a
+// vector register through it.
+__device__ __forceinline__ int lane_now() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
 }
 
 // acc + lo + hi of a packed pair of bf16 values (one v_dot2c_f32_bf16 against (1, 1)).
@@ -192,6 +202,10 @@ struct DmaCursor {
   __device__ __forceinline__ void load(uint16_t* tile, int wave) {
     const int valid = min(BN, rows);
     const __amdgpu_buffer_rsrc_t rs = tile_rsrc<D>(ptr, ss, valid);
+    // The LDS destinations are formed here from the wavefront number: hoisted out of the loop
+    // they would hold eight scalar registers, some of them spilled to vector lanes (at head dim
+    // 64, with half as many, they fit).
+    if constexpr (D == 128) asm volatile("" : "+s"(wave));
 #pragma unroll
     for (int i = 0; i < Layout<D, NW>::NLD; ++i) {
       const int blk = wave + NW * i;
@@ -208,7 +222,9 @@ struct DmaCursor {
 // segment. SEGM (with SEG, for a non-null seg_mass): each segment's log-sum-exp over the
 // launch's key range is recorded; an instance of its own, so that launches without it carry
 // none of its state (2% of the segment launch).
-template <int D, int BM, bool SEG, bool SEGM>
+// BARE: some of the launch's query rows want neither mass nor log-sum-exp; the kernel then holds
+// the key loop twice, with and without the fp32 row sums.
+template <int D, int BM, bool SEG, bool SEGM, bool BARE>
 __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
   constexpr int NW = BM / 32;  // wavefronts
   constexpr int KS = D / 16;   // MFMA k-steps over the head dim for S^T
@@ -225,6 +241,7 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const int g = lane >> 5, n = lane & 31;
 
   // ---- which (batch, head, query tile) and which key tiles this workgroup owns
@@ -251,7 +268,7 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
     rt0 = __builtin_amdgcn_s_memrealtime();
   }
   auto probe_end = [&]() {
-    if (probe && tid == 0) {
+    if (probe && wave_u == 0 && lane_now() == 0) {
       const uint64_t clk1 = __builtin_amdgcn_s_memtime(), rt1 = __builtin_amdgcn_s_memrealtime();
       atomicAdd(p.clock_probe, (unsigned long long)(clk1 - clk0));
       atomicAdd(p.clock_probe + 1, (unsigned long long)(rt1 - rt0));
@@ -278,6 +295,10 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
   const bool ref_rows = qt < qt_ref;
   if (!ref_rows) qt -= qt_ref;
 
+  // The query tile over key tiles [j0, j1); the rest of the kernel, not indented for its length.
+  // massc: the fp32 row sums are wanted, for the mass and the log-sum-exp.
+  auto run = [&](auto massc) __attribute__((always_inline)) {
+  constexpr bool MASS = decltype(massc)::value;
   // Reference queries over the cached K/V read the cached queries when the caller gave them.
   const View qv = ref_rows ? (use_cache && p.q_cache.p ? p.q_cache : p.q_ref) : p.q_tgt;
   const View ov = ref_rows ? p.o_ref : p.o_tgt;
@@ -295,7 +316,6 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
   const int rag_tgt = p.n_tgt % BN ? nt - 1 : -1;
   // Per-lane byte offsets of the direct loads, per source view (the segments of SEG share
   // the reference views' strides).
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const uint32_t voff_r = dma_lane_offset<true>(lane, krv.ss);
   const uint32_t voff_rv = dma_lane_offset<false>(lane, vrv.ss);
   const uint32_t voff_yk = dma_lane_offset<true>(lane, p.k_tgt.ss);
@@ -303,14 +323,13 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
   const int64_t kbh = b * krv.sb + h * krv.sh, vbh = b * vrv.sb + h * vrv.sh;  // SEG: this (b, h)
 
   // ---- this lane's query row; Q^T as the B operand (query n, head-dim chunk 2*kk + g)
-  const int qrow = qt * BM + wave * 32 + n;
-  const bool qvalid = qrow < n_rows;
   bf16x8 qreg[KS];
   {
+    const int qrow = qt * BM + wave * 32 + n;
     const uint16_t* qp = static_cast<const uint16_t*>(qv.p) + b * qv.sb + h * qv.sh + (int64_t)qrow * qv.ss;
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) {
-      const u32x4 raw = qvalid ? *reinterpret_cast<const u32x4*>(qp + kk * 16 + g * 8) : u32x4{0, 0, 0, 0};
+      const u32x4 raw = qrow < n_rows ? *reinterpret_cast<const u32x4*>(qp + kk * 16 + g * 8) : u32x4{0, 0, 0, 0};
       qreg[kk] = __builtin_bit_cast(bf16x8, raw);
     }
   }
@@ -409,19 +428,18 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
     while (seg_idx < p.n_seg && j0 >= seg_end_tab[seg_idx]) ++seg_idx;
   const int seg_first = seg_idx;
   int seg_end_t = SEG && seg_idx < p.n_seg ? seg_end_tab[seg_idx] : -1;
-  const int64_t seg_row = ((int64_t)bh * p.n_tgt + qrow) * p.n_seg;
-  const int64_t seg_prow = ((int64_t)slot * BM + wave * 32 + n) * p.n_seg;
   // Closes the current segment: records its log-sum-exp (log2 domain) over this key range,
   // which the epilogue or the merge turns into a mass, then folds its sum into the reference
   // statistics, each kept against its own max, and restarts the running sum.
   auto close_segment = [&]() {
     const float l_seg = xor32_add(l_run);  // whole wavefront: the swap reads the partner lane
-    if (!ref_rows && qvalid && g == 0) {
+    const int ln = lane_now(), tile_row = wave_u * 32 + (ln & 31), qrow = qt * BM + tile_row;
+    if (!ref_rows && qrow < n_rows && ln < 32) {
       const float lse_s = m_run + __log2f(l_seg);
       if (slot >= 0)
-        p.part_seg[seg_prow + seg_idx] = lse_s;
+        p.part_seg[((int64_t)slot * BM + tile_row) * p.n_seg + seg_idx] = lse_s;
       else
-        p.seg_mass[seg_row + seg_idx] = lse_s;
+        p.seg_mass[((int64_t)bh * p.n_tgt + qrow) * p.n_seg + seg_idx] = lse_s;
     }
     l_ref = seg_idx == seg_first ? l_run : l_ref * __builtin_amdgcn_exp2f(m_ref - m_run) + l_run;
     m_ref = m_run;
@@ -432,8 +450,8 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
 
   // jbc: the LDS buffer of K_j and V_j, (j - j0) & 1, as a compile-time constant. firstc: the
   // workgroup's first tile, which has no earlier probabilities to multiply with V.
-  auto iteration = [&](auto jbc, auto firstc, int j, f32x16(&s_cur)[2], f32x16(&s_next)[2], uint32_t(&p_prev)[4][4],
-                       uint32_t(&p_cur)[4][4]) __attribute__((always_inline)) {
+  auto iteration = [&](auto jbc, auto firstc, int j, f32x16(&s_cur)[2], f32x16(&s_next)[2],
+                       uint32_t(&p_prev)[4][4], uint32_t(&p_cur)[4][4]) __attribute__((always_inline)) {
     constexpr int jb = decltype(jbc)::value;
     constexpr bool FIRST = decltype(firstc)::value;
     constexpr int PV = FIRST ? 0 : NPV;  // MFMAs of O += V_{j-1}^T P_{j-1}^T
@@ -446,12 +464,15 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
     // The ragged last tile of each of the reference and target segments (if any) is known
     // up front: the test in the loop compares tile indices only.
     if (j == rag_ref || j == rag_tgt) {  // ragged last tile of a segment: drop keys past its end
-      const int valid = tile_valid(j);
+      // Keys formed from `g` are hoisted out of the loop into 32 registers. Head dim 64 has them
+      // to spare, and its loop is scheduled better with them (1-4% on launches of many tiles); at
+      // head dim 128 they left none for the second key loop.
+      const int valid = tile_valid(j), gn = D == 64 ? g : lane_now() >> 5;
 #pragma unroll
       for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int key = 32 * mb + 16 * (r >> 3) + 8 * g + (r & 7);
+          const int key = 32 * mb + 16 * (r >> 3) + 8 * gn + (r & 7);
           if (key >= valid) s_cur[mb][r] = -__builtin_inff();
         }
     }
@@ -485,6 +506,7 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
     // Adds a pair to its row-sum chain; the first pair of a chain starts it (0 + x is not
     // folded away: it would turn -0 into +0).
     auto row_add = [&](int q, float e0, float e1) {
+      if constexpr (!MASS) return;
       if (q < 8) {
         rs_a = q == 0 ? e0 + e1 : rs_a + (e0 + e1);
         pin(rs_a);
@@ -559,10 +581,24 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
       for (int k = i * 18 / NS; k < (i + 1) * 18 / NS; ++k) pipe_step(k);
       __builtin_amdgcn_sched_barrier(0);
     }
+    // The rounded sum of the tile's P, after its last MFMA has issued: in the MFMA slots the
+    // dot2 instructions slowed the matrix core's issue (+8% against +2.5% here).
+    float s01, s23;
+    auto rounded_sum = [&]() __attribute__((always_inline)) {
+      __builtin_amdgcn_sched_barrier(0);
+      s01 = s23 = 0.f;
+#pragma unroll
+      for (int wd = 0; wd < 8; ++wd) {
+        s01 = add_bf16x2(p_cur[wd >> 2][wd & 3], s01);
+        s23 = add_bf16x2(p_cur[2 + (wd >> 2)][wd & 3], s23);
+      }
+    };
     // Probabilities against the running max: a lane's partial row sum bounds each of its
     // terms, so a sum within PBOUND (NaN and inf fail the test) proves that none exceeds
-    // it and the running max may stay; otherwise a cold path moves the max.
-    if (__any(!(rs_a + rs_b <= PBOUND))) {
+    // it and the running max may stay; otherwise a cold path moves the max. The test takes the
+    // fp32 sum, or the rounded one where that is the only one.
+    if constexpr (!MASS) rounded_sum();
+    if (__any(!((MASS ? rs_a + rs_b : s01 + s23) <= PBOUND))) {
       // Rare (always at a workgroup's first tile): move the max to the tile's row max
       // (nothing of this tile is in O^T yet) and form the probabilities again.
       float mx = s_cur[1][0];
@@ -573,7 +609,7 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
       for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s_cur[0][r]);
       m_new = fmaxf(xor32_max(mx) * c, m_run);
       const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-      l_run *= alpha;
+      if constexpr (MASS) l_run *= alpha;
       lo_run *= alpha;
 #pragma unroll
       for (int i = 0; i < DB; ++i) o[i] *= alpha;
@@ -586,23 +622,17 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
         row_add(q, e0, e1);
         pack(q, e0, e1);
       }
+      if constexpr (!MASS) rounded_sum();
     }
-    l_run += rs_a + rs_b;
-    // The rounded sum of the tile's P after its last MFMA has issued: in the MFMA slots the
-    // dot2 instructions slowed the matrix core's issue (+8% against +2.5% here).
-    __builtin_amdgcn_sched_barrier(0);
-    {
-      float s01 = 0.f, s23 = 0.f;
-#pragma unroll
-      for (int wd = 0; wd < 8; ++wd) {
-        s01 = add_bf16x2(p_cur[wd >> 2][wd & 3], s01);
-        s23 = add_bf16x2(p_cur[2 + (wd >> 2)][wd & 3], s23);
-      }
-      lo_run += s01 + s23;
-      pin(lo_run);
+    if constexpr (MASS) {
+      l_run += rs_a + rs_b;
+      rounded_sum();
     }
+    lo_run += s01 + s23;
+    pin(lo_run);
 
-    if (SEGM) {  // per-segment statistics
+    if constexpr (!MASS) {
+    } else if (SEGM) {  // per-segment statistics
       if (j + 1 == seg_end_t) close_segment();  // end of reference segment seg_idx
     } else if (j == n_rt - 1) {  // end of the reference segment: freeze its statistics
       m_ref = m_run;
@@ -614,15 +644,24 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
   // O += V_j^T P_j^T of the last tile (in LDS buffer jbc), whose probabilities no iteration follows.
   auto last_pv = [&](auto jbc, uint32_t(&pl)[4][4]) __attribute__((always_inline)) {
     const uint16_t* vs = decltype(jbc)::value ? vbuf1 : vbuf0;
-#pragma unroll
-    for (int i = 0; i < NPV; ++i) {
-      const int s2 = i / DB;
+    auto v_operand = [&](int i) {
       const uint16_t* a = vs + v_lane + 512 * i;
       const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(a));
       const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(a + 128));
-      const bf16x8 va = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+    bf16x8 va[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) va[i] = v_operand(i);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NPV; ++i) {
+      const int s2 = i / DB;
       const u32x4 pwv = {pl[s2][0], pl[s2][1], pl[s2][2], pl[s2][3]};
-      o[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, __builtin_bit_cast(bf16x8, pwv), o[i % DB], 0, 0, 0);
+      o[i % DB] =
+          __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i & 3], __builtin_bit_cast(bf16x8, pwv), o[i % DB], 0, 0, 0);
+      if (i + 4 < NPV) va[i & 3] = v_operand(i + 4);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
 
@@ -653,20 +692,23 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
     }
   }
 
+  const int lane_e = lane_now();
+  const int ge = lane_e >> 5, tile_row = wave_u * 32 + (lane_e & 31), qrow = qt * BM + tile_row;
+  const bool qvalid = qrow < n_rows;
   const float lo_sum = xor32_add(lo_run);  // both lanes of a query hold half its keys
   const float l_sum = xor32_add(l_run), l_ref_sum = xor32_add(l_ref);
   // ---- epilogue of a key chunk: unnormalised output and statistics to the workspace
   if (slot >= 0) {
     if (qvalid) {
-      const int64_t prow = (int64_t)slot * BM + wave * 32 + n;
+      const int64_t prow = (int64_t)slot * BM + tile_row;
       float* po = p.part_o + prow * D;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr)
-          *reinterpret_cast<float4*>(po + 32 * db + 8 * rr + 4 * g) =
+          *reinterpret_cast<float4*>(po + 32 * db + 8 * rr + 4 * ge) =
               float4{o[db][4 * rr], o[db][4 * rr + 1], o[db][4 * rr + 2], o[db][4 * rr + 3]};
-      if (g == 0) {
+      if (ge == 0) {
         p.part_st[prow] = float4{m_run, l_sum, m_ref, l_ref_sum};
         p.part_lo[prow] = lo_sum;
       }
@@ -692,9 +734,9 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
         } pk;
 #pragma unroll
         for (int i = 0; i < 4; ++i) pk.h[i] = (__bf16)(o[db][4 * rr + i] * inv_o);
-        *reinterpret_cast<u32x2*>(op + 32 * db + 8 * rr + 4 * g) = pk.w;
+        *reinterpret_cast<u32x2*>(op + 32 * db + 8 * rr + 4 * ge) = pk.w;
       }
-    if (g == 0) {
+    if (ge == 0) {
       const float mass = L_R * inv;
       const int64_t row = (int64_t)bh * n_rows + qrow;
       if (!ref_rows) {
@@ -710,11 +752,21 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
       if (SEGM && !ref_rows) {  // per-segment log-sum-exp -> mass, in place
         const float lt = m_run + __log2f(total);
         for (int s2 = 0; s2 < p.n_seg; ++s2)
-          p.seg_mass[seg_row + s2] = __builtin_amdgcn_exp2f(p.seg_mass[seg_row + s2] - lt);
+          p.seg_mass[row * p.n_seg + s2] = __builtin_amdgcn_exp2f(p.seg_mass[row * p.n_seg + s2] - lt);
       }
     }
   }
   probe_end();
+  };
+  // Query rows whose mass and log-sum-exp nobody asked for (the reference rows of most launches)
+  // skip the fp32 row sums: 32 of a tile's 144 vector instructions.
+  if constexpr (BARE) {
+    if (!(ref_rows ? p.mass_refq != nullptr : p.mass_tgt != nullptr || p.lse_tgt != nullptr)) {
+      run(std::false_type{});
+      return;
+    }
+  }
+  run(std::true_type{});
 }
 
 // Combines the key chunks of split query tiles: one row per D/4 threads, four
@@ -743,16 +795,26 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const SplitPlan&
   const int qrow = qt * BM + rr;
   if (qrow >= n_rows) return;
 
-  // Both passes load MERGE_BATCH chunks' partials before using any (one memory round trip
-  // per batch instead of per chunk) and combine them in chunk order.
+  // MERGE_BATCH chunks' partials are loaded before any is used and combined in chunk order. A
+  // split of at most MERGE_BATCH chunks is one memory round trip: the max comes from the same
+  // loads. More chunks take the max first, from their statistics alone.
   const int nc = pl.chunks;
   const int64_t base = (int64_t)st * nc * BM + rr;  // partial row of chunk 0
-  float M = -__builtin_inff(), M_R = -__builtin_inff();
-  for (int c0 = 0; c0 < nc; c0 += MERGE_BATCH) {
-    float4 sv[MERGE_BATCH];
+  float4 sv[MERGE_BATCH], ov4[MERGE_BATCH];
+  float lv[MERGE_BATCH];
+  auto load_batch = [&](int c0) {
 #pragma unroll
-    for (int u = 0; u < MERGE_BATCH; ++u)
-      if (c0 + u < nc) sv[u] = p.part_st[base + (int64_t)(c0 + u) * BM];
+    for (int u = 0; u < MERGE_BATCH; ++u) {
+      if (c0 + u < nc) {
+        const int64_t prow = base + (int64_t)(c0 + u) * BM;
+        sv[u] = p.part_st[prow];
+        lv[u] = p.part_lo[prow];
+        ov4[u] = *reinterpret_cast<const float4*>(p.part_o + prow * D + col);
+      }
+    }
+  };
+  float M = -__builtin_inff(), M_R = -__builtin_inff();
+  auto max_batch = [&](int c0) {
 #pragma unroll
     for (int u = 0; u < MERGE_BATCH; ++u) {
       if (c0 + u < nc) {
@@ -760,22 +822,23 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const SplitPlan&
         if (sv[u].w > 0.f) M_R = fmaxf(M_R, sv[u].z);
       }
     }
+  };
+  if (nc <= MERGE_BATCH) {
+    load_batch(0);
+    max_batch(0);
+  } else {
+    for (int c0 = 0; c0 < nc; c0 += MERGE_BATCH) {
+#pragma unroll
+      for (int u = 0; u < MERGE_BATCH; ++u)
+        if (c0 + u < nc) sv[u] = p.part_st[base + (int64_t)(c0 + u) * BM];
+      max_batch(c0);
+    }
   }
   float L_Rr = 0.f, L_Y = 0.f;  // L_Rr: reference sum against M_R
   float L_o = 0.f;              // sum of the rounded probabilities that entered O
   float4 acc{0.f, 0.f, 0.f, 0.f};
   for (int c0 = 0; c0 < nc; c0 += MERGE_BATCH) {
-    float4 sv[MERGE_BATCH], ov[MERGE_BATCH];
-    float lv[MERGE_BATCH];
-#pragma unroll
-    for (int u = 0; u < MERGE_BATCH; ++u) {
-      if (c0 + u < nc) {
-        const int64_t prow = base + (int64_t)(c0 + u) * BM;
-        sv[u] = p.part_st[prow];
-        lv[u] = p.part_lo[prow];
-        ov[u] = *reinterpret_cast<const float4*>(p.part_o + prow * D + col);
-      }
-    }
+    if (nc > MERGE_BATCH) load_batch(c0);
 #pragma unroll
     for (int u = 0; u < MERGE_BATCH; ++u) {
       if (c0 + u < nc) {
@@ -783,10 +846,10 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const SplitPlan&
         L_Y += sv[u].y * wgt;
         L_o += lv[u] * wgt;
         if (sv[u].w > 0.f) L_Rr += sv[u].w * __builtin_amdgcn_exp2f(sv[u].z - M_R);
-        acc.x += ov[u].x * wgt;
-        acc.y += ov[u].y * wgt;
-        acc.z += ov[u].z * wgt;
-        acc.w += ov[u].w * wgt;
+        acc.x += ov4[u].x * wgt;
+        acc.y += ov4[u].y * wgt;
+        acc.z += ov4[u].z * wgt;
+        acc.w += ov4[u].w * wgt;
       }
     }
   }
@@ -857,25 +920,33 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p) {
 
 // Explicit instantiations: without them the host pass leaves the segment instances, which
 // are only reached through the launcher's kernel-pointer argument, without launch stubs.
-template __global__ void attn_bf16_kernel<128, 256, false, false>(AttnParams);
-template __global__ void attn_bf16_kernel<64, 256, false, false>(AttnParams);
-template __global__ void attn_bf16_kernel<128, 128, false, false>(AttnParams);
-template __global__ void attn_bf16_kernel<64, 128, false, false>(AttnParams);
-template __global__ void attn_bf16_kernel<128, 256, true, false>(AttnParams);
-template __global__ void attn_bf16_kernel<64, 256, true, false>(AttnParams);
-template __global__ void attn_bf16_kernel<128, 256, true, true>(AttnParams);
-template __global__ void attn_bf16_kernel<64, 256, true, true>(AttnParams);
+template __global__ void attn_bf16_kernel<128, 256, false, false, false>(AttnParams);
+template __global__ void attn_bf16_kernel<64, 256, false, false, false>(AttnParams);
+template __global__ void attn_bf16_kernel<128, 256, false, false, true>(AttnParams);
+template __global__ void attn_bf16_kernel<64, 256, false, false, true>(AttnParams);
+template __global__ void attn_bf16_kernel<128, 128, false, false, false>(AttnParams);
+template __global__ void attn_bf16_kernel<64, 128, false, false, false>(AttnParams);
+template __global__ void attn_bf16_kernel<128, 128, false, false, true>(AttnParams);
+template __global__ void attn_bf16_kernel<64, 128, false, false, true>(AttnParams);
+template __global__ void attn_bf16_kernel<128, 256, true, false, false>(AttnParams);
+template __global__ void attn_bf16_kernel<64, 256, true, false, false>(AttnParams);
+template __global__ void attn_bf16_kernel<128, 256, true, true, false>(AttnParams);
+template __global__ void attn_bf16_kernel<64, 256, true, true, false>(AttnParams);
 
 template <int D, int BM>
 hipError_t launch_plain(const AttnParams& p, dim3 grid, hipStream_t stream) {
-  return launch_kernel(attn_bf16_kernel<D, BM, false, false>, grid, dim3(2 * BM), 0, stream, p);
+  // The instance with both key loops only where a launch has rows for the bare one: its larger
+  // code costs the others up to 1% (reuse launches 0.3%, launches of a few tiles 1%).
+  const bool bare = (p.qt_ref > 0 && !p.mass_refq) || !(p.mass_tgt || p.lse_tgt);
+  return bare ? launch_kernel(attn_bf16_kernel<D, BM, false, false, true>, grid, dim3(2 * BM), 0, stream, p)
+              : launch_kernel(attn_bf16_kernel<D, BM, false, false, false>, grid, dim3(2 * BM), 0, stream, p);
 }
 
 template <int D>
 hipError_t launch_segments(const AttnParams& p, dim3 grid, hipStream_t stream) {
   constexpr int BM = kAttnBf16BM;
-  return p.seg_mass ? launch_kernel(attn_bf16_kernel<D, BM, true, true>, grid, dim3(2 * BM), 0, stream, p)
-                    : launch_kernel(attn_bf16_kernel<D, BM, true, false>, grid, dim3(2 * BM), 0, stream, p);
+  return p.seg_mass ? launch_kernel(attn_bf16_kernel<D, BM, true, true, false>, grid, dim3(2 * BM), 0, stream, p)
+                    : launch_kernel(attn_bf16_kernel<D, BM, true, false, false>, grid, dim3(2 * BM), 0, stream, p);
 }
 
 template <int D, int BM>
@@ -919,10 +990,10 @@ AttnSlots attn_bf16_slots(int head_dim, int bm) {
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0);
   };
   const hipError_t e =
-      bi ? (di ? occupancy(attn_bf16_kernel<128, kAttnBf16SmallBM, false, false>, 2 * kAttnBf16SmallBM)
-               : occupancy(attn_bf16_kernel<64, kAttnBf16SmallBM, false, false>, 2 * kAttnBf16SmallBM))
-         : (di ? occupancy(attn_bf16_kernel<128, kAttnBf16BM, false, false>, 2 * kAttnBf16BM)
-               : occupancy(attn_bf16_kernel<64, kAttnBf16BM, false, false>, 2 * kAttnBf16BM));
+      bi ? (di ? occupancy(attn_bf16_kernel<128, kAttnBf16SmallBM, false, false, false>, 2 * kAttnBf16SmallBM)
+               : occupancy(attn_bf16_kernel<64, kAttnBf16SmallBM, false, false, false>, 2 * kAttnBf16SmallBM))
+         : (di ? occupancy(attn_bf16_kernel<128, kAttnBf16BM, false, false, false>, 2 * kAttnBf16BM)
+               : occupancy(attn_bf16_kernel<64, kAttnBf16BM, false, false, false>, 2 * kAttnBf16BM));
   if (e != hipSuccess || per_cu < 1 || cus < 1) return AttnSlots{0, 0};
   if (dev < 64) {
     cache[dev][di][bi][1].store(per_cu, std::memory_order_relaxed);

@@ -60,3 +60,53 @@ def test_small_launches_against_the_oracle(D, H, n_ref, n_tgt):
         # outputs reach the size of a value where one key dominates: bf16 rounds them by 2^-9 of it
         assert max_abs(host(o), ref["o"]) <= O_TOL["bf16"] + 2.0 ** -8 * np.abs(ref["o"]).max()
         assert max_abs(host(m), ref["ref_mass"]) <= MASS_TOL["bf16"]
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("H,n_ref,n_tgt", [(2, 700, 300), (128, 769, 449)])
+@pytest.mark.parametrize("kind", ["plain", "spikes"])
+@pytest.mark.parametrize("split", [False, True])
+def test_rows_without_mass_keep_their_outputs(D, H, n_ref, n_tgt, kind, split):
+    """Rows that want neither mass nor log-sum-exp take the loop without the fp32 row sums. Their
+    outputs differ at most where the running max moves at another tile: a bf16 rounding of the
+    probabilities and one of the result (2^-8 of the largest output)."""
+    from paper_2609_32415_amd import ops
+
+    print(f"D {D} H {H} n_ref {n_ref} n_tgt {n_tgt} {kind} split {split}", flush=True)
+    x = _tensors(H, D, n_ref, n_tgt, kind)
+    kw = dict(q_ref=x["q_ref"], k_ref=x["k_ref"], v_ref=x["v_ref"], qset="all", kvsrc="fresh",
+              workspace=None if split else False)
+    run = lambda **f: ops.joint_attn(x["q_tgt"], x["k_tgt"], x["v_tgt"], **kw, **f)
+    all_ = run(ref_mass=True, lse=True, ref_mass_refq=True)
+    tgt = run(ref_mass=True, lse=True)
+    none = run(ref_mass=False)
+    lse = run(ref_mass=False, lse=True)
+    torch.cuda.synchronize()
+    for got in (tgt, none, lse):
+        for a, b in ((all_.o_tgt, got.o_tgt), (all_.o_ref, got.o_ref)):
+            assert max_abs(host(a), host(b)) <= 2.0 ** -8 * float(a.float().abs().max())
+    assert torch.equal(all_.o_tgt, tgt.o_tgt) and torch.equal(all_.ref_mass, tgt.ref_mass)
+    assert torch.equal(all_.lse, tgt.lse) and torch.equal(all_.lse, lse.lse)
+    assert none.ref_mass is None and none.lse is None
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("decision", [0, 1, 2])
+def test_device_decided_rows_without_mass(D, decision):
+    from paper_2609_32415_amd import ops
+
+    x = _tensors(24, D, 1100, 700, "plain")
+    c = {k: (v.float() * 1.03).to(torch.bfloat16) for k, v in x.items() if k.endswith("ref")}
+    print(f"D {D} decision {decision}", flush=True)
+    dec = torch.tensor([decision], dtype=torch.int32, device="cuda:0")
+    got = ops.joint_attn(x["q_tgt"], x["k_tgt"], x["v_tgt"], q_ref=x["q_ref"], k_ref=x["k_ref"], v_ref=x["v_ref"],
+                         k_cache=c["k_ref"], v_cache=c["v_ref"], q_cache=c["q_ref"], kvsrc="device", decision=dec)
+    src = x if decision == 2 else c
+    want = ops.joint_attn(x["q_tgt"], x["k_tgt"], x["v_tgt"], q_ref=src["q_ref"], k_ref=src["k_ref"],
+                          v_ref=src["v_ref"], qset="all", kvsrc="fresh", ref_mass_refq=True, workspace=False)
+    torch.cuda.synchronize()
+    bar = 2.0 ** -8
+    assert max_abs(host(got.o_tgt), host(want.o_tgt)) <= bar * float(want.o_tgt.float().abs().max())
+    assert max_abs(host(got.ref_mass), host(want.ref_mass)) <= 1e-5
+    if decision:
+        assert max_abs(host(got.o_ref), host(want.o_ref)) <= bar * float(want.o_ref.float().abs().max())
