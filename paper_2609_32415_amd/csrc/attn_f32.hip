@@ -20,11 +20,12 @@
 // LDS, the same reduction the online softmax performs across key tiles; no workspace is needed.
 //
 // Bound: the fp32 matrix rate, 32 cycles per product and SIMD (256 FLOP/clk/CU; 153 TFLOP/s on a
-// large library product). Measured at 24 heads of 128, 1101 + 1024 keys: all queries 0.60 ms (93
-// TFLOP/s), target queries 0.27 ms (98 TFLOP/s); 8 heads of 128, 2048 + 2048 keys, all queries
-// 0.57 ms (119 TFLOP/s). One row per lane on the vector ALU, as this path was written before,
-// took 7.7 ms for the first. What is left: two or three wavefronts per SIMD do not hide all of
-// the wait for the global loads (without them, -7%) and the barrier.
+// large library product). Measured at 24 heads of 128, 1101 + 1024 keys: all queries 0.58 ms (95
+// TFLOP/s), target queries 0.27 ms (99 TFLOP/s); 8 heads of 128, 2048 + 2048 keys, all queries
+// 0.53 ms (130 TFLOP/s). One row per lane on the vector ALU, as this path was written before,
+// took 8.8 ms for the first. What is left: the last, partly filled round of workgroups, and the
+// vector instructions, which do not overlap the products (40 fewer a tile by bare exponentials
+// and a max without canonicalisation gave 2-8%; later stores or earlier loads gave nothing).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -37,6 +38,26 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 
 constexpr float RAISE = 8.f;  // log2 of how far a probability may exceed 1 before the max moves
+
+// Largest of the four values of each of one or two accumulators (NaNs ignored, as fmaxf does):
+// fmaxf would first canonicalise every operand. The compiler does not place the wait states that
+// an instruction in asm needs after a matrix instruction wrote its operand (11 for these) and
+// before a lane swap reads its result, so the block holds them.
+__device__ __forceinline__ float max_of(const f32x4 (&v)[1]) {
+  float r;
+  asm("s_nop 15\n\tv_max3_f32 %0, %1, %2, %3\n\tv_max_f32 %0, %0, %4\n\ts_nop 1"
+      : "=&v"(r)
+      : "v"(v[0][0]), "v"(v[0][1]), "v"(v[0][2]), "v"(v[0][3]));
+  return r;
+}
+__device__ __forceinline__ float max_of(const f32x4 (&v)[2]) {
+  float r;
+  asm("s_nop 15\n\tv_max3_f32 %0, %1, %2, %3\n\tv_max3_f32 %0, %0, %4, %5\n\tv_max3_f32 %0, %0, %6, %7\n\t"
+      "v_max_f32 %0, %0, %8\n\ts_nop 1"
+      : "=&v"(r)
+      : "v"(v[0][0]), "v"(v[0][1]), "v"(v[0][2]), "v"(v[0][3]), "v"(v[1][0]), "v"(v[1][1]), "v"(v[1][2]), "v"(v[1][3]));
+  return r;
+}
 
 // A value combined over the query's four lane groups (lanes l, l ^ 16, l ^ 32, l ^ 48).
 __device__ __forceinline__ float quad_max(float v) {
@@ -277,22 +298,21 @@ f32x4 a[2][MB];
         for (int r = 0; r < 4; ++r)
           if (16 * mb + 4 * g + r >= valid) sc[mb][r] = -__builtin_inff();
     }
-    // the products of tile j + 1 with the softmax of tile j under them
+    // The products of tile j + 1 with the softmax of tile j under them. The exponentials are the
+    // bare instruction, which returns zero below 2^-126: next to the row's largest probability
+    // (at least 1 at some key so far) nothing of that size enters a sum.
     float alpha;
     auto softmax = [&]() __attribute__((always_inline)) {
-      float mx = fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3]));
-#pragma unroll
-      for (int mb = 1; mb < MB; ++mb) mx = fmaxf(mx, fmaxf(fmaxf(sc[mb][0], sc[mb][1]), fmaxf(sc[mb][2], sc[mb][3])));
       // The max moves only when it would grow by more than RAISE: until then a probability is at
       // most 2^RAISE, which fp32 holds as exactly as one below 1, and O is not rescaled.
-      const float m_tile = quad_max(mx) * c;
+      const float m_tile = quad_max(max_of(sc)) * c;
       const float m_new = m_tile > m_run + RAISE ? m_tile : m_run;
-      alpha = exp2f(m_run - m_new);
+      alpha = __builtin_amdgcn_exp2f(m_run - m_new);
       float rs = 0.f;
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sc[mb][r] = exp2f(fmaf(sc[mb][r], c, -m_new));
+        for (int r = 0; r < 4; ++r) sc[mb][r] = __builtin_amdgcn_exp2f(fmaf(sc[mb][r], c, -m_new));
         rs += (sc[mb][0] + sc[mb][1]) + (sc[mb][2] + sc[mb][3]);
       }
       l_run = l_run * alpha + rs;

@@ -64,7 +64,7 @@ __global__ __launch_bounds__(PF_THREADS) void pair_final(const float2* ws, PairS
   const int npairs = kind == PAIR_SINGLE ? 1 : 2;
   // pair pr's records of (b, h) lie at ws[(pr * bh_total + bh) * chunks_max + c]; those with
   // c >= chunks[pr] were not written and are not added
-  for (int pr = 0; pr < npairs; ++pr) stage_partials(s_part[pr], ws + (int64_t)pr * bh_total * chunks_max, h0, nh, chunks_max);
+  for (int pr = 0; pr < npairs; ++pr) stage_partials<4>(s_part[pr], ws + (int64_t)pr * bh_total * chunks_max, h0, nh, chunks_max);
   __syncthreads();
   if ((int)threadIdx.x >= nh) return;
   const int bh = h0 + threadIdx.x;

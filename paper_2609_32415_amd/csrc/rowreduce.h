@@ -17,6 +17,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int QC_THREADS = 256;
 constexpr int QC_TARGET_ELEMS = 16384;  // elements of one tensor per workgroup (32 KiB of bf16)
 constexpr int QC_MAX_CHUNKS = 64;
+constexpr int QC_SMALL_ELEMS = 2048;  // smallest chunk of a slice of fewer than QC_SMALL_CHUNKS full ones
+constexpr int QC_SMALL_CHUNKS = 8;
 constexpr int QC_UNROLL = 8;  // 16-byte vectors of each tensor per thread in flight
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -32,24 +34,23 @@ __device__ __forceinline__ float wave_sum(float v) {
 // Stages the chunk partials of heads [h0, h0 + nh) (`chunks` records of T per head, head
 // major) in LDS with coalesced loads by the whole workgroup, head i at s[i * (chunks + 1)]
 // (the padding spreads the per-head rows over the banks).
-// STAGE_UNROLL records of a thread are in flight at once: the records come from other XCDs'
-// workgroups, so each round trip costs about a microsecond (24 heads x 34 records: pair_final
-// 5.2 -> 4.0 us; eight in flight measured the same).
-constexpr int STAGE_UNROLL = 4;
-
-template <typename T>
+// UNROLL records of a thread are in flight at once: the records come from other XCDs'
+// workgroups, so each round trip costs about a microsecond (pair_final over 24 heads x 34 records
+// 5.2 -> 4.0 us with four; eight measured the same; the gate's single workgroup, bound by its
+// chain of dependent steps and by fetching its code, takes one: 2.1 us against 2.4 with four).
+template <int UNROLL, typename T>
 __device__ __forceinline__ void stage_partials(T* s, const T* part, int h0, int nh, int chunks) {
   const int n = nh * chunks;
   const T* src = part + (int64_t)h0 * chunks;
-  for (int i0 = threadIdx.x; i0 < n; i0 += STAGE_UNROLL * blockDim.x) {
-    T v[STAGE_UNROLL];
+  for (int i0 = threadIdx.x; i0 < n; i0 += UNROLL * blockDim.x) {
+    T v[UNROLL];
 #pragma unroll
-    for (int u = 0; u < STAGE_UNROLL; ++u) {
+    for (int u = 0; u < UNROLL; ++u) {
       const int i = i0 + u * blockDim.x;
       if (i < n) v[u] = src[i];
     }
 #pragma unroll
-    for (int u = 0; u < STAGE_UNROLL; ++u) {
+    for (int u = 0; u < UNROLL; ++u) {
       const int i = i0 + u * blockDim.x;
       if (i < n) s[i + i / chunks] = v[u];
     }

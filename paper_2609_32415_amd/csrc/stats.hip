@@ -39,7 +39,7 @@ __global__ __launch_bounds__(QF_THREADS) void q_change_final(const float2* ws, i
   __shared__ float2 s_part[QF_HEADS * (QC_MAX_CHUNKS + 1)];
   const int h0 = blockIdx.x * QF_HEADS;
   const int nh = min(QF_HEADS, bh_total - h0);
-  stage_partials(s_part, ws, h0, nh, chunks);
+  stage_partials<4>(s_part, ws, h0, nh, chunks);
   __syncthreads();
   if ((int)threadIdx.x >= nh) return;
   const float2* r = s_part + threadIdx.x * (chunks + 1);
@@ -204,12 +204,14 @@ __global__ __launch_bounds__(QC_THREADS) void q_change_mass_partial(View cur, Vi
   }
 }
 
-constexpr int QG_THREADS = 256;
-constexpr int QG_STAGE = 1024;  // float4 partial records staged in LDS per round (16 KiB)
+// One workgroup reads every partial record, so its threads are its loads in flight: 22 heads x 64
+// chunks 6.7 us with 256 threads and two rounds of 1024 records, 4.0 us with these.
+constexpr int QG_THREADS = 1024;
+constexpr int QG_STAGE = 2048;  // float4 partial records staged in LDS per round (32 KiB)
 
 // Pass 2 of the fused Q-change + gate (one workgroup): rounds of (b, h) pairs have their
 // chunk partials staged in LDS (one coalesced memory round trip per round, a single round
-// up to 1024 / chunks pairs); one thread per pair adds them in chunk order in fp64 and
+// up to QG_STAGE / chunks pairs); one thread per pair adds them in chunk order in fp64 and
 // writes D and the mean lagged mass; then thread 0 decides.
 __global__ __launch_bounds__(QG_THREADS) void q_change_gate_final(const float4* part, int32_t BH, int32_t chunks,
                                                                   int32_t n_rows, float eps, int32_t block,
@@ -224,7 +226,7 @@ __global__ __launch_bounds__(QG_THREADS) void q_change_gate_final(const float4* 
   const int per_round = max(1, min(QG_THREADS, QG_STAGE / chunks));
   for (int h0 = 0; h0 < BH; h0 += per_round) {
     const int nh = min(per_round, BH - h0);
-    stage_partials(s_part, part, h0, nh, chunks);
+    stage_partials<1>(s_part, part, h0, nh, chunks);
     __syncthreads();
     if ((int)threadIdx.x < nh) {
       const float4* r = s_part + threadIdx.x * (chunks + 1);
@@ -272,9 +274,15 @@ __global__ __launch_bounds__(CC_THREADS) void cache_commit_kernel(CommitSet cs, 
 
 }  // namespace
 
+// Chunks of QC_TARGET_ELEMS elements; up to QC_SMALL_CHUNKS smaller ones of a short slice, whose
+// few workgroups would leave the memory idle (2 heads of 256 x 64 fp32: two workgroups reading
+// 128 KiB each took 4.8 us, sixteen of 16 KiB 3.8 us). The most heads the gate takes
+// (8192) times these chunks still fit the fixed scratch of the allocation-free variant.
 int q_change_chunks(int32_t n_tgt, int32_t head_dim) {
   const int64_t elems = (int64_t)n_tgt * head_dim;
+  const int64_t small = (elems + QC_SMALL_ELEMS - 1) / QC_SMALL_ELEMS;
   int64_t c = (elems + QC_TARGET_ELEMS - 1) / QC_TARGET_ELEMS;
+  if (c < QC_SMALL_CHUNKS) c = small < QC_SMALL_CHUNKS ? small : QC_SMALL_CHUNKS;
   if (c < 1) c = 1;
   if (c > QC_MAX_CHUNKS) c = QC_MAX_CHUNKS;
   if (c > n_tgt) c = n_tgt;

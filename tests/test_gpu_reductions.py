@@ -54,3 +54,25 @@ def test_second_passes(H, n):
         d_r, d_t, _ = ops.drift_log_ratio(a, b, b[:, :, :s], a[:, :, :s])
         np.testing.assert_allclose(host(d_r), host(ab), rtol=rtol)
         np.testing.assert_allclose(host(d_t), host(norm(b[:, :, :s].double() - a[:, :, :s].double()) / norm(a[:, :, :s])), rtol=rtol)
+
+
+@pytest.mark.parametrize("H,n,d", [(8192, 4, 64), (1025, 40, 64), (33, 7000, 128), (2, 256, 64), (3, 9, 128), (5, 145, 128)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_gate_final_rounds(H, n, d, dtype):
+    """Heads around the rounds of the gate's one workgroup (as many as its threads or its staged
+    records allow, up to the most heads the gate takes), and slices of one to eight small chunks."""
+    from paper_2609_32415_amd import ops
+
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(H + n)
+    print(f"H {H} n {n} d {d} {dtype}", flush=True)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    a, b = (torch.randn((1, H, n, d), generator=g, device="cuda:0").to(dt) for _ in range(2))
+    mass = torch.rand((1, H, n), generator=g, device="cuda:0")
+    theta = torch.full((1,), float("inf"), device="cuda:0")
+    got, _, scores = ops.q_change_gate(a, b, mass, theta, ops.new_gate_state("cuda:0"), 0, 1)
+    norm = lambda x: x.double().square().sum((2, 3)).sqrt()
+    want, m = norm(a.double() - b.double()) / norm(b), mass.double().mean(-1)
+    rtol = 128 * 2.0 ** -24  # as above
+    np.testing.assert_allclose(host(got), host(want), rtol=rtol)
+    np.testing.assert_allclose(host(scores), [float(want.mean()), float(m.mean()), float((want * m).mean())], rtol=rtol)
