@@ -1,7 +1,8 @@
 // Joint attention over [reference; target] keys on bf16 MFMA (gfx950).
 //
-// One workgroup = 8 wavefronts = 256 query rows of one (batch, head); each
-// wavefront owns 32 query rows. Key/value tiles of 64 rows stream through LDS,
+// One workgroup = 8 wavefronts = 256 query rows of one (batch, head), or half as
+// many of both in small launches (the host chooses); each wavefront owns 32 query
+// rows. Key/value tiles of 64 rows stream through LDS,
 // reference tiles first (from the fresh or the cached reference K/V, chosen
 // once per workgroup) and then target tiles.
 //
@@ -28,10 +29,11 @@
 // V_j; the iteration's one barrier, after a wait for those loads, publishes
 // them.
 //
-// One workgroup fills a CU with two wavefronts per SIMD (at most 256 vector
-// registers per lane each): while one wavefront forms probabilities the other
-// keeps the matrix core busy, and the eight wavefronts share every K/V tile
-// in LDS (each wavefront loads two 1 KiB blocks of each tile).
+// One workgroup of 256 rows (or two of 128) fills a CU with two wavefronts per SIMD (at most
+// 256 vector registers per lane each): while one wavefront forms probabilities the other
+// keeps the matrix core busy, and a workgroup's wavefronts share every K/V tile
+// in LDS. At head dim 64 a third wavefront per SIMD fits the registers and gave nothing: the
+// loop is bound by the instructions it issues and the power they take, not by latency.
 //
 // Online softmax in the exp2 domain without a per-tile row max: probabilities
 // are formed against the running max m, and a lane's partial row sum bounds
@@ -42,13 +44,14 @@
 // the scores, rescales O and l, and forms the probabilities again. The
 // O rescale and the row max are thus almost never executed.
 // Row sums add the fp32 probabilities, so the reference mass and the
-// log-sum-exp carry no bf16 rounding. Rows that want neither (the reference rows of most
-// launches) skip them and take the bound test on the rounded sum below: 2.78 -> 2.71 ms at 24
-// heads of 128, 12544 of the 16640 queries bare; 467 -> 455 us at 24 heads of 64, 4352 of 8448. O is divided by a second sum, that of
+// log-sum-exp carry no bf16 rounding. O is divided by a second sum, that of
 // the bf16-rounded probabilities it accumulated (one v_dot2c_f32_bf16 per
 // packed pair, after the tile's last MFMA), so the weights
 // applied to V sum to one: with the fp32 sum, the rounding of a dominant
 // probability (relative error up to 2^-8) moved the output by as much of V.
+// Rows that want neither mass nor log-sum-exp ("bare": the reference rows of most launches)
+// skip the fp32 sums and take the bound test on the rounded one: 2.78 -> 2.71 ms at 24 heads of
+// 128, 12544 of the 16640 queries bare; 467 -> 455 us at 24 heads of 64, 4352 of 8448.
 //
 // Split statistics for the reference mass (paper Sec. 3.2, directional
 // exposure): after the last reference tile the running (max, sum) pair is
