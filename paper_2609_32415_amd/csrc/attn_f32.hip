@@ -36,7 +36,6 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-
 constexpr float RAISE = 8.f;  // log2 of how far a probability may exceed 1 before the max moves
 
 // Largest of the four values of each of one or two accumulators (NaNs ignored, as fmaxf does):
@@ -464,11 +463,13 @@ hipError_t launch(const AttnParams& p, hipStream_t stream) {
 // subtiles per workgroup (and so more key groups) spread a small launch over more CUs and waste
 // less of the last round, many share a K/V tile between more wavefronts. `lone` and `full` are
 // the measured time per unit of each shape with one workgroup on a CU and with several, relative
-// to (QW 4, several): 17.6 ns per key at head dim 128.
-//   us, shapes QW 4 / 2 / 1:  24 heads, 1101 + 1024, all queries 600 / 596 / 600; target queries
-//   305 / 273 / 284; 48 heads of 64, 2000 + 1900, target 871 / 908 / 977; 6 heads, 700 + 500, all
-//   103 / 65 / 60; 2 heads, 2000 + 100, target 175 / 107 / 58; 2 heads of 64, 256 + 256, all
-//   29 / 19 / 12.
+// to (QW 4, several): 16.5 ns per key at head dim 128.
+//   us, shapes QW 4 / 2 / 1:  24 heads, 1101 + 1024, all queries 558 / 584 / 596; target queries
+//   283 / 278 / 282; 48 heads of 64, 2000 + 1900, target 804 / 885 / 981; 6 heads, 700 + 500, all
+//   96 / 63 / 68; 2 heads, 2000 + 100, target 163 / 104 / 54; 2 heads of 64, 256 + 256, all
+//   26 / 19 / 12.
+// Where two shapes are estimated within a few percent (the first launch takes QW 2) fewer keys per
+// sum also mean a smaller error: 9.2e-7 / 7.1e-7 / 5.8e-7 there.
 // The choice weighs the launch with and without the reference queries alike and does not depend
 // on which of the two this is, so target rows are summed in the same order in both.
 struct Split {
