@@ -599,9 +599,28 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
     // Probabilities against the running max: a lane's partial row sum bounds each of its
     // terms, so a sum within PBOUND (NaN and inf fail the test) proves that none exceeds
     // it and the running max may stay; otherwise a cold path moves the max. The test takes the
-    // fp32 sum, or the rounded one where that is the only one.
+    // fp32 sum. Rows without one take the rounded sum, each of whose terms is within 2^-9 of the
+    // fp32 one, against a bound lower by more than that, and form the fp32 sum only where this
+    // fails: the max moves at the same tiles, and O has the same bits, with and without the fp32
+    // sums.
     if constexpr (!MASS) rounded_sum();
-    if (__any(!((MASS ? rs_a + rs_b : s01 + s23) <= PBOUND))) {
+    bool move_max = __any(!(MASS ? rs_a + rs_b <= PBOUND : s01 + s23 <= PBOUND * (1.f - 1.f / 128.f)));
+    if constexpr (!MASS && !FIRST) {
+      if (move_max) {
+        float m = m_run;
+        pin(m);  // else the loop's exponent arguments would be kept for this, in 32 registers
+        float sum[2] = {};
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          const int mb = q >> 3, o2 = (2 * q) & 15;
+          const float e = __builtin_amdgcn_exp2f(fmaf(s_cur[mb][o2], c, -m)) +
+                          __builtin_amdgcn_exp2f(fmaf(s_cur[mb][o2 + 1], c, -m));
+          sum[mb] = (q & 7) == 0 ? e : sum[mb] + e;
+        }
+        move_max = __any(!(sum[0] + sum[1] <= PBOUND));
+      }
+    }
+    if (move_max) {
       // Rare (always at a workgroup's first tile): move the max to the tile's row max
       // (nothing of this tile is in O^T yet) and form the probabilities again.
       float mx = s_cur[1][0];
