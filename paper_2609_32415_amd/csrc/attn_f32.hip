@@ -37,6 +37,10 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float RAISE = 8.f;  // log2 of how far a probability may exceed 1 before the max moves
+// The running max before any key: the lowest finite value, so that keys that score -inf (a product
+// that overflows, a masked key) add nothing wherever they stand, in a tile, a key group or a row;
+// against -inf their difference would be NaN.
+constexpr float LOWEST = -__FLT_MAX__;
 
 // Largest of the four values of each of one or two accumulators (NaNs ignored, as fmaxf does):
 // fmaxf would first canonicalise every operand. The compiler does not place the wait states that
@@ -245,15 +249,17 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnParams p) {
   for (int i = 0; i < DB; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   // l_run and l_ref hold this lane's share of the query's keys; the four lane groups of a
   // query see the same max and are added at the end.
-  float m_run = -__builtin_inff(), l_run = 0.f, m_ref = -__builtin_inff(), l_ref = 0.f;
-  const float c = p.sc_log2;
+  // Maxima are unscaled scores: (score - max) is exact for the scores near the max, where a max
+  // rounded after scaling would be off by its own rounding, 2^7 in log2 at scores of 2^32.
+  float m_run = LOWEST, l_run = 0.f, m_ref = LOWEST, l_ref = 0.f;
+  const float c = p.sc_log2, raise = RAISE / c;
 
   // scores of the K tile in buffer `buf`
   auto scores = [&](f32x4(&sc)[MB], int buf) __attribute__((always_inline)) {
     const float* ks = kbuf + (S::NBUF > 1 ? buf : 0) * TK * KSTR + n * KSTR + 4 * g;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) sc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-f32x4 a[2][MB];
+    f32x4 a[2][MB];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -304,14 +310,14 @@ f32x4 a[2][MB];
     auto softmax = [&]() __attribute__((always_inline)) {
       // The max moves only when it would grow by more than RAISE: until then a probability is at
       // most 2^RAISE, which fp32 holds as exactly as one below 1, and O is not rescaled.
-      const float m_tile = quad_max(max_of(sc)) * c;
-      const float m_new = m_tile > m_run + RAISE ? m_tile : m_run;
-      alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      const float m_tile = quad_max(max_of(sc));
+      const float m_new = m_tile > m_run + raise ? m_tile : m_run;
+      alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);
       float rs = 0.f;
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sc[mb][r] = __builtin_amdgcn_exp2f(fmaf(sc[mb][r], c, -m_new));
+        for (int r = 0; r < 4; ++r) sc[mb][r] = __builtin_amdgcn_exp2f((sc[mb][r] - m_new) * c);
         rs += (sc[mb][0] + sc[mb][1]) + (sc[mb][2] + sc[mb][3]);
       }
       l_run = l_run * alpha + rs;
@@ -404,19 +410,19 @@ f32x4 a[2][MB];
       M = fmaxf(M, rec[k * STEP + 64 * S::OREGS]);
       M_R = fmaxf(M_R, rec[k * STEP + 64 * (S::OREGS + 2)]);
     }
-    // a group without keys, or without reference keys, has a max of -inf and adds nothing
-    float w = exp2f(m_run - M);
+    // a group without keys has sums of zero
+    float w = exp2f((m_run - M) * c);
     l_run *= w;
-    L_Rr = l_ref > 0.f ? l_ref * exp2f(m_ref - M_R) : 0.f;
+    L_Rr = l_ref > 0.f ? l_ref * exp2f((m_ref - M_R) * c) : 0.f;
 #pragma unroll
     for (int i = 0; i < DB; ++i) o[i] *= w;
 #pragma unroll
     for (int k = 0; k < KW - 1; ++k) {
       const float* r0 = rec + k * STEP;
-      w = exp2f(r0[64 * S::OREGS] - M);
+      w = exp2f((r0[64 * S::OREGS] - M) * c);
       l_run += r0[64 * (S::OREGS + 1)] * w;
       const float lr = r0[64 * (S::OREGS + 3)];
-      if (lr > 0.f) L_Rr += lr * exp2f(r0[64 * (S::OREGS + 2)] - M_R);
+      if (lr > 0.f) L_Rr += lr * exp2f((r0[64 * (S::OREGS + 2)] - M_R) * c);
 #pragma unroll
       for (int i = 0; i < DB; ++i)
 #pragma unroll
@@ -425,7 +431,7 @@ f32x4 a[2][MB];
     m_run = M;
   }
   if (!qvalid) return;
-  L_R = L_Rr > 0.f ? L_Rr * exp2f(M_R - m_run) : 0.f;
+  L_R = L_Rr > 0.f ? L_Rr * exp2f((M_R - m_run) * c) : 0.f;
   const float sum = L_R + l_run, inv = 1.f / sum;
   float* op = static_cast<float*>(const_cast<void*>(ov.p)) + b * ov.sb + h * ov.sh + (int64_t)qrow * ov.ss;
 #pragma unroll
@@ -441,8 +447,8 @@ f32x4 a[2][MB];
     if (p.mass_tgt) p.mass_tgt[row] = mass;
     if (p.lse_tgt) {
       const float ln2 = 0.69314718055994531f;
-      p.lse_tgt[2 * row] = (M_R + log2f(L_Rr)) * ln2;
-      p.lse_tgt[2 * row + 1] = (m_run + log2f(sum)) * ln2;
+      p.lse_tgt[2 * row] = fmaf(M_R, c, log2f(L_Rr)) * ln2;
+      p.lse_tgt[2 * row + 1] = fmaf(m_run, c, log2f(sum)) * ln2;
     }
   } else if (p.mass_refq) {
     p.mass_refq[row] = mass;
