@@ -20,12 +20,15 @@
 // LDS, the same reduction the online softmax performs across key tiles; no workspace is needed.
 //
 // Bound: the fp32 matrix rate, 32 cycles per product and SIMD (256 FLOP/clk/CU; 153 TFLOP/s on a
-// large library product). Measured at 24 heads of 128, 1101 + 1024 keys: all queries 0.58 ms (95
-// TFLOP/s), target queries 0.27 ms (99 TFLOP/s); 8 heads of 128, 2048 + 2048 keys, all queries
-// 0.53 ms (130 TFLOP/s). One row per lane on the vector ALU, as this path was written before,
-// took 8.8 ms for the first. What is left: the last, partly filled round of workgroups, and the
-// vector instructions, which do not overlap the products (40 fewer a tile by bare exponentials
-// and a max without canonicalisation gave 2-8%; later stores or earlier loads gave nothing).
+// large library product). Measured at 24 heads of 128, 1101 + 1024 keys: all queries 0.60 ms (93
+// TFLOP/s), target queries 0.27 ms (98 TFLOP/s); 8 heads of 128, 2048 + 2048 keys, all queries
+// 0.56 ms (124 TFLOP/s). One row per lane on the vector ALU, as this path was written before,
+// took 7.8 ms for the first. What is left: the last, partly filled round of workgroups, and the
+// vector instructions, which do not overlap the products (later stores or earlier loads gave
+// nothing). Two per score keep the type's range: a square that keeps subnormal probabilities, and
+// the difference to the unscaled max instead of one FMA. The max moves with every larger score, so
+// no probability exceeds one and O overflows only where its sum does. Without the three, and
+// with a max that lagged by up to 2^8, the times above were 0.59, 0.27 and 0.54 ms.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -36,11 +39,24 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr float RAISE = 8.f;  // log2 of how far a probability may exceed 1 before the max moves
 // The running max before any key: the lowest finite value, so that keys that score -inf (a product
 // that overflows, a masked key) add nothing wherever they stand, in a tile, a key group or a row;
 // against -inf their difference would be NaN.
 constexpr float LOWEST = -__FLT_MAX__;
+
+// 2^(2 x): the bare exponential returns zero below 2^-126, its square keeps the subnormal
+// probabilities, which a value near the largest fp32 still carries into the output.
+__device__ __forceinline__ float exp2_twice(float x) {
+  const float h = __builtin_amdgcn_exp2f(x);
+  return h * h;
+}
+
+// x / sum for inv = 1 / sum <= 1: the product, corrected by its remainder to the rounded quotient
+// (Markstein); an infinite or NaN x has no remainder.
+__device__ __forceinline__ float divide(float x, float sum, float inv) {
+  const float q = x * inv, r = fmaf(-q, sum, x);
+  return fabsf(r) <= __FLT_MAX__ ? fmaf(r, inv, q) : q;
+}
 
 // Largest of the four values of each of one or two accumulators (NaNs ignored, as fmaxf does):
 // fmaxf would first canonicalise every operand. The compiler does not place the wait states that
@@ -252,7 +268,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnParams p) {
   // Maxima are unscaled scores: (score - max) is exact for the scores near the max, where a max
   // rounded after scaling would be off by its own rounding, 2^7 in log2 at scores of 2^32.
   float m_run = LOWEST, l_run = 0.f, m_ref = LOWEST, l_ref = 0.f;
-  const float c = p.sc_log2, raise = RAISE / c;
+  const float c = p.sc_log2, hc = 0.5f * c;
 
   // scores of the K tile in buffer `buf`
   auto scores = [&](f32x4(&sc)[MB], int buf) __attribute__((always_inline)) {
@@ -303,21 +319,17 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnParams p) {
         for (int r = 0; r < 4; ++r)
           if (16 * mb + 4 * g + r >= valid) sc[mb][r] = -__builtin_inff();
     }
-    // The products of tile j + 1 with the softmax of tile j under them. The exponentials are the
-    // bare instruction, which returns zero below 2^-126: next to the row's largest probability
-    // (at least 1 at some key so far) nothing of that size enters a sum.
+    // The products of tile j + 1 with the softmax of tile j under them.
     float alpha;
     auto softmax = [&]() __attribute__((always_inline)) {
-      // The max moves only when it would grow by more than RAISE: until then a probability is at
-      // most 2^RAISE, which fp32 holds as exactly as one below 1, and O is not rescaled.
       const float m_tile = quad_max(max_of(sc));
-      const float m_new = m_tile > m_run + raise ? m_tile : m_run;
-      alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);
+      const float m_new = m_tile > m_run ? m_tile : m_run;
+      alpha = exp2_twice((m_run - m_new) * hc);
       float rs = 0.f;
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sc[mb][r] = __builtin_amdgcn_exp2f((sc[mb][r] - m_new) * c);
+        for (int r = 0; r < 4; ++r) sc[mb][r] = exp2_twice((sc[mb][r] - m_new) * hc);
         rs += (sc[mb][0] + sc[mb][1]) + (sc[mb][2] + sc[mb][3]);
       }
       l_run = l_run * alpha + rs;
@@ -439,7 +451,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnParams p) {
 #pragma unroll
     for (int r = 0; r < 4; ++r)
       *reinterpret_cast<f32x4*>(op + 64 * hh + 4 * (4 * g + r)) =
-          f32x4{o[4 * hh][r] * inv, o[4 * hh + 1][r] * inv, o[4 * hh + 2][r] * inv, o[4 * hh + 3][r] * inv};
+          f32x4{divide(o[4 * hh][r], sum, inv), divide(o[4 * hh + 1][r], sum, inv), divide(o[4 * hh + 2][r], sum, inv),
+                divide(o[4 * hh + 3][r], sum, inv)};
   if (g != 0) return;
   const int64_t row = (int64_t)bh * n_rows + qrow;
   const float mass = L_R / sum;

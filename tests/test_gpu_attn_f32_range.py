@@ -1,5 +1,6 @@
 """fp32 attention at the ends of the type's range: keys that score -inf or the lowest values in whole
-tiles and key groups, and scores far beyond 2^24."""
+tiles and key groups, scores far beyond 2^24, probabilities below 2^-126 and values near the largest
+fp32."""
 
 import numpy as np
 import pytest
@@ -88,3 +89,52 @@ def test_scores_far_beyond_the_mantissa(shape, size):
     for s, lo, m, o in (("ref", 0, n_ref, got.o_ref), ("tgt", n_ref, n_tgt, got.o_tgt)):
         pick = np.where(sign[lo:lo + m] > 0, top[..., None], low[..., None])
         assert np.array_equal(host(o), np.take_along_axis(v, pick[..., None], 2))
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "-".join(map(str, s)))
+def test_subnormal_probabilities_reach_the_output(shape):
+    """One key at score 0 and value 0, the rest at 2^-130 in probability and 1.5 * 2^127 in value.
+    The score scale's and the exponent argument's roundings are 2^-24 of 130 each, a probability's
+    2^-150 of 2^-130."""
+    _, D, B, H, n_ref, n_tgt = shape
+    print(f"shape {shape}", flush=True)
+    n = n_ref + n_tgt
+    x = {}
+    for s, lo, m in (("ref", 0, n_ref), ("tgt", n_ref, n_tgt)):
+        for k in "qkv":
+            x[f"{k}_{s}"] = np.zeros((B, H, m, D), np.float32)
+        x[f"q_{s}"][..., 0] = 1.0
+        x[f"k_{s}"][..., 0] = -130.0
+        x[f"v_{s}"][..., :] = 1.5 * 2.0 ** 127 / n
+    x["k_tgt"][:, :, 0, 0] = 0.0
+    x["v_tgt"][:, :, 0] = 0.0
+    got = _run(x, scale=float(np.log(2.0)))
+    want = 1.5 * 2.0 ** -3 * (n - 1) / n
+    bar = 4 * 130 * 2.0 ** -24 + 2.0 ** -20 + n * 2.0 ** -24
+    for o in (got.o_tgt, got.o_ref):
+        assert np.abs(host(o) / want - 1.0).max() <= bar
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "-".join(map(str, s)))
+@pytest.mark.parametrize("step", [0.0, 4.0, 7.9])
+def test_the_largest_values_do_not_overflow(shape, step):
+    """A last key `step` above the others in log2, whose value is 0.99 of the largest fp32 and
+    theirs a thousandth over the number of keys: no partial sum may exceed the result by much."""
+    _, D, B, H, n_ref, n_tgt = shape
+    print(f"shape {shape} {step}", flush=True)
+    n = n_ref + n_tgt
+    top = 0.99 * float(np.finfo(np.float32).max)
+    x = {}
+    for s, m in (("ref", n_ref), ("tgt", n_tgt)):
+        for k in "qkv":
+            x[f"{k}_{s}"] = np.zeros((B, H, m, D), np.float32)
+        x[f"q_{s}"][..., 0] = 1.0
+        x[f"v_{s}"][...] = top / n * 1e-3
+    x["k_tgt"][:, :, -1, 0] = step
+    x["v_tgt"][:, :, -1] = top
+    got = _run(x, scale=float(np.log(2.0)))
+    w = 2.0 ** step
+    want = (w * top + (n - 1) * top / n * 1e-3) / (w + n - 1)
+    bar = (n + 4 * 8) * 2.0 ** -24
+    for o in (got.o_tgt, got.o_ref):
+        assert np.abs(host(o) / want - 1.0).max() <= bar
