@@ -32,6 +32,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "internal.h"
 
 namespace refadapt {
@@ -156,8 +158,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnParams p) {
   }
   const int per_bh = qt_ref - first + qt_tgt;
   const int total = p.B * p.H * per_bh;
-  if ((int)blockIdx.x >= total) return;
-  const int tile = xcd_remap(blockIdx.x, total);
+  const int item = p.block0 + (int)blockIdx.x;
+  if (item >= total) return;
+  const int tile = xcd_remap(item, total);
   const int bh = tile / per_bh;
   int qt = tile - bh * per_bh + first;
   const int b = bh / p.H, h = bh - b * p.H;
@@ -474,7 +477,17 @@ hipError_t launch(const AttnParams& p, hipStream_t stream) {
   const int64_t per_bh = (p.qt_ref > 0 ? (p.n_ref + BQ - 1) / BQ : 0) + (p.n_tgt + BQ - 1) / BQ;
   const int64_t total = (int64_t)p.B * p.H * per_bh;
   if (total > 0x7fffffff) return hipErrorInvalidValue;
-  return launch_kernel(attn_f32_kernel<D, NW, QW, TK>, dim3((unsigned)total), dim3(64 * NW), 0, stream, p);
+  // One launch holds fewer than 2^32 threads: with a few rows per (batch, head) and millions of
+  // these the workgroups take several.
+  constexpr int64_t per_launch = (int64_t)0xffffffff / (64 * NW) & ~7;
+  AttnParams q = p;
+  for (int64_t first = 0; first < total; first += per_launch) {
+    q.block0 = (int32_t)first;
+    const unsigned n = (unsigned)std::min(per_launch, total - first);
+    const hipError_t e = launch_kernel(attn_f32_kernel<D, NW, QW, TK>, dim3(n), dim3(64 * NW), 0, stream, q);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // The split of a launch. Every workgroup of QW query subtiles costs QW units of work, so a

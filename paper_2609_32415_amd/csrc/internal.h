@@ -48,6 +48,7 @@ struct AttnParams {
   int32_t qt_tgt;       // query tiles per (b, h) over target rows
   int32_t total_tiles;  // B * H * (qt_ref + qt_tgt) = grid size
   int32_t kvsrc;
+  int32_t block0;  // fp32 path: this launch's first workgroup among those of the call
   float sc_log2;  // softmax scale * log2(e)
   // bf16 path: plan[0] covers the launch's query set (under KV_DEVICE: every
   // query tile), plan[1] the target query tiles alone (KV_DEVICE on REUSE).

@@ -1,6 +1,6 @@
 """fp32 attention at the ends of the type's range: keys that score -inf or the lowest values in whole
-tiles and key groups, scores far beyond 2^24, probabilities below 2^-126 and values near the largest
-fp32."""
+tiles and key groups, scores far beyond 2^24, probabilities below 2^-126, values near the largest
+fp32, and a launch of more workgroups than one grid holds threads for."""
 
 import numpy as np
 import pytest
@@ -138,3 +138,19 @@ def test_the_largest_values_do_not_overflow(shape, step):
     bar = (n + 4 * 8) * 2.0 ** -24
     for o in (got.o_tgt, got.o_ref):
         assert np.abs(host(o) / want - 1.0).max() <= bar
+
+
+def test_more_workgroups_than_one_grid_holds():
+    """17 million heads of one key: each output row is its value row."""
+    from paper_2609_32415_amd import ops
+
+    H = 17_000_000
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(1)
+    q = torch.ones((1, H, 1, 64), device="cuda:0")
+    v = torch.randn((1, H, 1, 64), generator=g, device="cuda:0")
+    print("launch", flush=True)
+    got = ops.joint_attn(q, q, v, ref_mass=True)
+    torch.cuda.synchronize()
+    assert torch.equal(got.o_tgt, v)
+    assert not got.ref_mass.any()
