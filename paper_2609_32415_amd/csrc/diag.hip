@@ -34,6 +34,7 @@ namespace {
 constexpr int MM_THREADS = 256;
 constexpr int MM_UNROLL = 8;
 constexpr int AC_THREADS = 64;
+constexpr int AC_BLOCKS = 1 << 20;  // workgroups of a launch (it holds fewer than 2^32 threads)
 
 // Pass 1: workgroup (chunk, bh, pair) sums (cur - base)^2 and base^2 over its rows.
 template <bool BF16>
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(MM_THREADS) void mass_mean_kernel(const float* mass
   }
 }
 
-// One wavefront per block, one lane per step: head means of the [T, n_blocks, bh] mass log, then
+// One wavefront per block at a time, one lane per step: head means of the [T, n_blocks, bh] mass log, then
 // 100 / (T - 1) * sum_t |mean_t - mean_{t-1}|. The time is memory latency: the steps' means are
 // independent, so AC_THREADS of them are formed at once, each in head order (fp64, as when one
 // thread walked all steps: 8 steps x 60 blocks x 24 heads 18.2 -> 3.0 us), and one lane adds the
@@ -125,30 +126,31 @@ __global__ __launch_bounds__(MM_THREADS) void mass_mean_kernel(const float* mass
 __global__ __launch_bounds__(AC_THREADS) void adjacent_change_kernel(const float* m, int32_t T, int32_t nb,
                                                                      int32_t bh, float* out) {
   __shared__ double means[AC_THREADS];
-  const int b = blockIdx.x;
-  double prev = 0.0, acc = 0.0;  // lane 0: the mean of the step before t0, the sum so far
-  for (int t0 = 0; t0 < T; t0 += AC_THREADS) {
-    const int t = t0 + threadIdx.x;
-    if (t < T) {
-      const float* row = m + ((int64_t)t * nb + b) * bh;
-      double s = 0.0;
+  for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
+    double prev = 0.0, acc = 0.0;  // lane 0: the mean of the step before t0, the sum so far
+    for (int64_t t0 = 0; t0 < T; t0 += AC_THREADS) {
+      const int64_t t = t0 + threadIdx.x;
+      if (t < T) {
+        const float* row = m + (t * nb + b) * bh;
+        double s = 0.0;
 #pragma unroll 8
-      for (int i = 0; i < bh; ++i) s += row[i];
-      means[threadIdx.x] = s / bh;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      const int n = min(AC_THREADS, T - t0);
-#pragma unroll 8
-      for (int i = 0; i < n; ++i) {
-        const double cur = means[i];
-        if (t0 + i > 0) acc += fabs(cur - prev);
-        prev = cur;
+        for (int i = 0; i < bh; ++i) s += row[i];
+        means[threadIdx.x] = s / bh;
       }
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        const int n = (int)std::min<int64_t>(AC_THREADS, T - t0);
+#pragma unroll 8
+        for (int i = 0; i < n; ++i) {
+          const double cur = means[i];
+          if (t0 + i > 0) acc += fabs(cur - prev);
+          prev = cur;
+        }
+      }
+      __syncthreads();
     }
-    __syncthreads();
+    if (threadIdx.x == 0) out[b] = (float)(100.0 * acc / (T - 1));
   }
-  if (threadIdx.x == 0) out[b] = (float)(100.0 * acc / (T - 1));
 }
 
 }  // namespace
@@ -184,7 +186,8 @@ hipError_t launch_mass_mean(int32_t B, int32_t H, int32_t n, const float* mass, 
 
 hipError_t launch_adjacent_change(int32_t T, int32_t nb, int32_t bh, const float* m, float* out,
                                   hipStream_t stream) {
-  return launch_kernel(adjacent_change_kernel, dim3(nb), dim3(AC_THREADS), 0, stream, m, T, nb, bh, out);
+  return launch_kernel(adjacent_change_kernel, dim3(std::min(nb, AC_BLOCKS)), dim3(AC_THREADS), 0, stream, m,
+                       T, nb, bh, out);
 }
 
 }  // namespace refadapt
