@@ -96,13 +96,18 @@ class Controller:
             q_prev = self.q_anchor[b] if t > 0 else x["q_tgt"]
         else:
             q_prev = self.q_prev[b] if self.q_prev[b] is not None else x["q_tgt"]
-        # one view op each (indexing with a slice or a pair of indices takes three times as long)
-        if not 0 <= t < self.decisions.shape[0]:
-            raise IndexError(f"step {t} is outside the trajectory's {self.decisions.shape[0]} steps")
-        cell = t * self.nb + b
-        dec = self.decisions.as_strided((1,), (1,), cell)
-        d, age = self.d.select(0, b), self.age.as_strided((1,), (1,), b)
-        score = self.scores.as_strided((3,), (1,), 3 * cell)
+        # one view op each (indexing takes about twice as long), at
+        # the tensors' own offsets and strides: a log may be a view of a larger one
+        if not (0 <= t < self.decisions.shape[0] and 0 <= b < self.nb):
+            raise IndexError(f"step {t}, block {b} is outside the trajectory's {self.decisions.shape[0]} steps "
+                             f"of {self.nb} blocks")
+        log, scores, ages = self.decisions, self.scores, self.age
+        ts, bs = log.stride()
+        dec = log.as_strided((1,), (1,), log.storage_offset() + t * ts + b * bs)
+        ts, bs, _ = scores.stride()
+        score = scores.as_strided((3,), (1,), scores.storage_offset() + t * ts + b * bs)
+        age = ages.as_strided((1,), (1,), ages.storage_offset() + b * ages.stride(0))
+        d = self.d.select(0, b)
         if self.fused:
             ops.q_change_gate(x["q_tgt"], q_prev, self.mass[b][self.parity[b]], self.theta, self.state, b, t,
                               self.mode, self.eps, d_out=d, decision_out=dec, score_out=score,
