@@ -106,7 +106,7 @@ typedef struct {
   float* lse_tgt;                /* out [B, H, n_tgt, 2] = (lse_ref, lse_all), or NULL */
   float* ref_mass_refq;          /* out [B, H, n_ref] reference-query mass on reference keys, or NULL */
   void* workspace;               /* device scratch for key-split partial results, or NULL (no split) */
-  size_t workspace_bytes;        /* its size; >= refadapt_joint_attn_workspace_size(desc) when non-NULL */
+  size_t workspace_bytes;        /* its size; refadapt_joint_attn_workspace_size(desc) when non-NULL (below) */
   /* Reference segments (used with RA_KV_SEGMENTS or a non-NULL seg_mass; else ignored):
    * segment s holds reference rows [seg_end[s-1], seg_end[s]) (seg_end[-1] = 0). */
   int32_t n_seg;                 /* 1..RA_MAX_SEG */
@@ -168,11 +168,18 @@ typedef struct {
  * round of workgroups are split into key-tile ranges whose partial softmax
  * statistics a second kernel merges (the same rescale-and-add the online
  * softmax applies across key tiles). Results then differ from the unsplit
- * launch only by fp32 rounding; a given desc on a given device always takes
- * the same split, so repeated calls are bitwise identical. With
- * workspace == NULL nothing is split. The workspace needs no initialisation,
- * must be 16-byte aligned and must not be used by another call that runs
- * concurrently. The fp32 path never splits.
+ * launch only by fp32 rounding (and that of the bf16 probabilities against the
+ * chunks' own maxima); a given desc on a given device with a workspace of a
+ * given size always takes the same split, so repeated calls are bitwise
+ * identical, and a device-decided launch gives the bits of the explicit launch
+ * of the queries it decides for. With workspace == NULL nothing is split. The
+ * workspace needs no initialisation, must be 16-byte aligned and must not be
+ * used by another call that runs concurrently. One workspace serves every kvsrc
+ * of a query set, and that of RA_KV_DEVICE both query sets: the size asked for
+ * does not depend on the K/V source. A workspace that holds less than the plan
+ * the library prefers, but the one on workgroups of 256 query rows, is taken
+ * too, for that plan. The fp32 path needs no workspace (it splits the keys of a
+ * row inside a workgroup, by the sizes alone).
  *
  * Errors: RA_EINVAL for a null desc/args, sizes out of range, unknown enums,
  * or a required pointer that is NULL (q/k/v/o_tgt always; k_ref/v_ref when
@@ -185,15 +192,17 @@ typedef struct {
  * RA_F32, RA_KV_DEVICE, an inner boundary off the 64-row key tiles, or (under
  * RA_KV_SEGMENTS) fresh and cached views with different strides, and (RA_BF16) for a
  * K/V row stride above 2^24 - 8 elements (key tiles use 32-bit offsets). RA_EWORKSPACE for a
- * non-NULL workspace smaller than refadapt_joint_attn_workspace_size(desc).
+ * non-NULL workspace too small for the plan on 256 query rows (never for one of
+ * refadapt_joint_attn_workspace_size(desc) bytes).
  */
 ra_status refadapt_joint_attn(const ra_attn_desc* desc, const ra_attn_args* args, void* stream);
 
 /*
  * refadapt_joint_attn_workspace_size - bytes of workspace that let
  * refadapt_joint_attn split key ranges for `desc` on the CURRENT device (the
- * split depends on the device's compute-unit count). 0 when no split pays or
- * for an invalid desc (refadapt_joint_attn then reports the error).
+ * split depends on the device's compute-unit count). The same for every kvsrc
+ * of a query set; for RA_KV_DEVICE the larger of both query sets'. 0 when no
+ * split pays or for an invalid desc (refadapt_joint_attn then reports the error).
  */
 size_t refadapt_joint_attn_workspace_size(const ra_attn_desc* desc);
 

@@ -13,6 +13,7 @@
 
 #include "refadapt.h"
 #include "internal.h"
+#include "plan.h"
 
 using namespace refadapt;
 
@@ -56,156 +57,21 @@ ra_status check_tensor(const char* name, const ra_tensor& t, int dtype, int32_t 
   return RA_OK;
 }
 
-// ---- work decomposition of the bf16 attention launch
-//
-// All query tiles of a launch cost the same (each attends to every key tile),
-// so the resident workgroups (slots = CUs x workgroups per CU) run them in
-// rounds. Cost model in units of "one key tile processed by every resident
-// workgroup": a round of items of L key tiles costs L, or kLoneRound * L when
-// the round holds no more items than there are CUs (a workgroup alone on its
-// CU runs faster); a chunk adds a fixed start-up and drain of kChunkOverhead
-// key tiles; the merge costs its partial-result traffic. The plan keeps the
-// largest number of whole rounds and splits only the remainder (plus, when it
-// pays, one more round) into chunks of at least kMinChunk key tiles.
-constexpr int kMinChunk = 4;
-constexpr double kChunkOverhead = 2.0;
-constexpr double kLoneRound = 0.67;
-constexpr int kMaxChunks = 32;
-
-SplitPlan whole_plan(int64_t tiles) {
-  return SplitPlan{(int32_t)tiles, 0, 1, (int32_t)tiles};
+// Sizes of a bf16 attention launch and the workgroups that the current device holds at once.
+PlanShape plan_shape(const ra_attn_desc& d) {
+  return PlanShape{(int64_t)d.batch * d.heads,
+                   d.head_dim,
+                   d.n_ref,
+                   d.n_tgt,
+                   attn_bf16_slots(d.head_dim, kAttnBf16BM),
+                   attn_bf16_slots(d.head_dim, kAttnBf16SmallBM)};
 }
 
-// Cost of running `items` items of `len` key tiles each in rounds of `slots`.
-double rounds_cost(int64_t items, double len, int64_t slots, int64_t cus) {
-  const int64_t full = items / slots, last = items - full * slots;
-  return full * len + (last == 0 ? 0.0 : last > cus ? len : kLoneRound * len);
-}
-
-SplitPlan plan_split(int64_t tiles, int nt, AttnSlots sl, int head_dim, int bm) {
-  SplitPlan best = whole_plan(tiles);
-  const int64_t slots = (int64_t)sl.cus * sl.per_cu;
-  if (tiles <= 0 || slots <= 0 || nt < 2 * kMinChunk) return best;
-  // A split must beat whole tiles by 3%; among splits the cheapest wins.
-  double best_cost = 0.97 * rounds_cost(tiles, nt, slots, sl.cus);
-  // Seconds for every resident workgroup to process one key tile (~1 PFLOP/s of
-  // attention) and to move one split item's partial rows twice (~4 TB/s).
-  const double tile_s = slots * 4.0 * bm * kAttnBf16BN * head_dim / 1.0e15;
-  const double item_s = 2.0 * bm * (head_dim + 4) * 4.0 / 4.0e12;
-  for (int extra = 0; extra < 2; ++extra) {
-    const int64_t rem = tiles % slots + (int64_t)extra * slots;
-    if (rem == 0 || rem > tiles) continue;
-    const int64_t rounds = (tiles - rem) / slots;
-    for (int c = 2; c <= kMaxChunks && c * kMinChunk <= nt; ++c) {
-      const int64_t items = rem * c;
-      if (items > 2 * slots) break;
-      const int chunk = (nt + c - 1) / c;
-      const double cost = (double)rounds * nt + rounds_cost(items, chunk + kChunkOverhead, slots, sl.cus) +
-                          (items * item_s + 5e-6) / tile_s;
-      if (cost < best_cost) {
-        best_cost = cost;
-        best = SplitPlan{(int32_t)(tiles - rem), (int32_t)rem, c, (int32_t)(tiles - rem + items)};
-      }
-    }
-  }
-  return best;
-}
-
-// Estimated time (us) of a plan on workgroups of bm query rows, to choose between the two
-// workgroup sizes. Time of one key tile in a round, measured per head dim with few workgroups
-// (one a CU at most, `lone`) and with a full round (`full`): 256-row workgroups keep a CU to
-// themselves and share a K/V tile between eight wavefronts; 128-row ones run two a CU, or one at
-// less time a tile, for twice the K/V traffic.
-struct TileTime {
-  double lone, full;
-};
-constexpr double kStartTiles = 2.0;  // start-up and drain of a workgroup, in key tiles
-constexpr double kMergeUs = 5.0;
-
-TileTime tile_time(int head_dim, int bm) {
-  if (bm == kAttnBf16BM) return head_dim == 128 ? TileTime{1.27, 1.62} : TileTime{1.02, 1.07};
-  return head_dim == 128 ? TileTime{0.95, 1.70} : TileTime{0.80, 1.06};
-}
-
-double plan_us(const SplitPlan& pl, int nt, AttnSlots sl, int head_dim, int bm) {
-  const TileTime tt = tile_time(head_dim, bm);
-  const int64_t cus = sl.cus, slots = cus * sl.per_cu;
-  const auto rounds = [&](int64_t items, double len) {
-    const int64_t full = items / slots, last = items - full * slots;
-    // a partly filled last round draws less power and runs at a higher clock
-    const double top = bm == kAttnBf16BM ? tt.full : tt.lone + 0.2;
-    const double part = last > cus ? tt.full : last > 0 ? tt.lone + (top - tt.lone) * (double)last / (double)cus : 0.0;
-    return len * ((double)full * tt.full + part);
-  };
-  double us = rounds(pl.whole, nt + kStartTiles);
-  if (pl.split_tiles > 0) {
-    const int64_t items = (int64_t)pl.split_tiles * pl.chunks;
-    us += rounds(items, (nt + pl.chunks - 1) / pl.chunks + kStartTiles) + kMergeUs +
-          (double)items * 2.0 * bm * (head_dim + 4) * 4.0 / 4.0e6;
-  }
-  return us;
-}
-
-// Plans of one bf16 launch (plan[0]: the launch's query set, plan[1]: target
-// query tiles only) and the workspace bytes their split items need.
-struct LaunchPlan {
-  SplitPlan plan[2];
-  int64_t qt_ref, qt_tgt;
-  int64_t items;  // split items of the larger plan
-  size_t ws_bytes;
-  size_t part_o_bytes;
-  int bm;         // query rows per tile
-  double us;      // estimated time of the plans
-};
-
-// Workspace bytes of a split launch that also records per-segment masses: the partials plus
-// one log-sum-exp per segment of each partial row, after them.
-size_t seg_ws_bytes(const LaunchPlan& lp, int n_seg) {
-  return lp.ws_bytes ? lp.ws_bytes + (size_t)lp.items * lp.bm * n_seg * sizeof(float) : 0;
-}
-
-LaunchPlan plan_launch_bm(const ra_attn_desc& d, bool split, int bm) {
-  LaunchPlan lp{};
-  lp.bm = bm;
-  const bool device = d.kvsrc == RA_KV_DEVICE;
-  const bool ref_queries = (device || d.qset == RA_Q_ALL) && d.n_ref > 0;
-  lp.qt_ref = ref_queries ? (d.n_ref + bm - 1) / bm : 0;
-  lp.qt_tgt = (d.n_tgt + bm - 1) / bm;
-  const int64_t bh = (int64_t)d.batch * d.heads;
-  const int64_t all = bh * (lp.qt_ref + lp.qt_tgt), tgt = bh * lp.qt_tgt;
-  lp.plan[0] = whole_plan(all);
-  lp.plan[1] = device ? whole_plan(tgt) : lp.plan[0];
-  if (d.dtype != RA_BF16 || all > 0x7fffffff) return lp;
-  const AttnSlots slots = attn_bf16_slots(d.head_dim, bm);
-  const int nt = (d.n_ref + kAttnBf16BN - 1) / kAttnBf16BN + (d.n_tgt + kAttnBf16BN - 1) / kAttnBf16BN;
-  if (split) {
-    lp.plan[0] = plan_split(all, nt, slots, d.head_dim, bm);
-    lp.plan[1] = device ? plan_split(tgt, nt, slots, d.head_dim, bm) : lp.plan[0];
-    int64_t items = 0;
-    for (const SplitPlan& pl : lp.plan) items = std::max<int64_t>(items, (int64_t)pl.split_tiles * pl.chunks);
-    lp.items = items;
-    lp.part_o_bytes = (size_t)items * bm * d.head_dim * sizeof(float);
-    lp.ws_bytes = items > 0 ? lp.part_o_bytes + (size_t)items * bm * 5 * sizeof(float) : 0;
-  }
-  if (slots.cus > 0) {
-    lp.us = plan_us(lp.plan[0], nt, slots, d.head_dim, bm);
-    if (device) lp.us += plan_us(lp.plan[1], nt, slots, d.head_dim, bm);
-  }
-  return lp;
-}
-
-// The launch runs workgroups of 128 query rows where the estimate says that they are 5% faster
-// (the estimates' own error), else of 256: launches of few tiles, which leave CUs idle or one
-// workgroup each. Measured, us, 256 against 128 rows: 4 heads, 300 + 256 tokens, all queries
-// 21.8 / 15.9; 24 heads, 1024 target queries over 2048 keys 43.6 / 38.3; 12 heads, 700 + 800, all
-// 40.8 / 30.5; 24 heads, 2095 + 1009, all 133 / 135; 24 heads, 4352 + 4096, all 755 / 778. The
-// segment kernel runs 256 rows only. Whole (unsplit) rows are summed in the same order in both.
-LaunchPlan plan_launch(const ra_attn_desc& d, bool split, bool seg) {
-  if (d.dtype != RA_BF16) return plan_launch_bm(d, split, kAttnF32BM);
-  const LaunchPlan big = plan_launch_bm(d, split, kAttnBf16BM);
-  if (seg || !(big.us > 0.0)) return big;
-  const LaunchPlan small = plan_launch_bm(d, split, kAttnBf16SmallBM);
-  return small.us > 0.0 && small.us < 0.95 * big.us ? small : big;
+// The query sets of a launch: with no reference rows, or without their queries, the target rows;
+// a device-decided launch holds both plans.
+LaunchMode launch_mode(const ra_attn_desc& d, bool seg) {
+  const bool device = d.kvsrc == RA_KV_DEVICE, all = (device || d.qset == RA_Q_ALL) && d.n_ref > 0;
+  return LaunchMode{all, device || !all, seg};
 }
 
 ra_status check_attn_desc(const ra_attn_desc* desc, const char* who) {
@@ -237,15 +103,15 @@ const char* refadapt_last_error(void) { return g_last_error.c_str(); }
 const char* refadapt_version(void) { return "refadapt 0.1 gfx950"; }
 
 size_t refadapt_joint_attn_workspace_size(const ra_attn_desc* desc) {
-  if (check_attn_desc(desc, "joint_attn_workspace_size") != RA_OK) return 0;
-  return plan_launch(*desc, true, desc->kvsrc == RA_KV_SEGMENTS).ws_bytes;
+  if (check_attn_desc(desc, "joint_attn_workspace_size") != RA_OK || desc->dtype != RA_BF16) return 0;
+  return launch_ws_bytes(plan_launch(plan_shape(*desc), true), launch_mode(*desc, false), desc->head_dim);
 }
 
 size_t refadapt_joint_attn_seg_workspace_size(const ra_attn_desc* desc, int32_t n_seg) {
   if (check_attn_desc(desc, "joint_attn_seg_workspace_size") != RA_OK) return 0;
   const ra_attn_desc& d = *desc;
   if (n_seg < 1 || n_seg > RA_MAX_SEG || d.dtype != RA_BF16 || d.kvsrc == RA_KV_DEVICE || d.n_ref < 1) return 0;
-  return seg_ws_bytes(plan_launch(d, true, true), n_seg);
+  return launch_seg_ws_bytes(plan_launch(plan_shape(d), true), launch_mode(d, true), d.head_dim, n_seg);
 }
 
 ra_status refadapt_joint_attn(const ra_attn_desc* desc, const ra_attn_args* args, void* stream) {
@@ -255,9 +121,10 @@ ra_status refadapt_joint_attn(const ra_attn_desc* desc, const ra_attn_args* args
   const ra_attn_desc& d = *desc;
   const ra_attn_args& a = *args;
   const bool device = d.kvsrc == RA_KV_DEVICE;
-  const bool ref_queries = (device || d.qset == RA_Q_ALL) && d.n_ref > 0;
   // Reference segments: per-segment K/V sources or per-segment masses.
   const bool seg = d.kvsrc == RA_KV_SEGMENTS || a.seg_mass != nullptr;
+  const LaunchMode mode = launch_mode(d, seg);
+  const bool ref_queries = mode.all;
   uint32_t seg_cache = 0;
   if (seg) {
     if (d.dtype != RA_BF16) return fail(RA_EUNSUPPORTED, "joint_attn: reference segments need RA_BF16");
@@ -346,29 +213,6 @@ ra_status refadapt_joint_attn(const ra_attn_desc* desc, const ra_attn_args* args
   const float scale = d.scale > 0.f ? d.scale : 1.0f / std::sqrt((float)d.head_dim);
   p.sc_log2 = scale * 1.4426950408889634f;
 
-  // Per-segment masses split key ranges only when the workspace also holds the per-segment
-  // partials; with a smaller workspace the launch runs whole query tiles.
-  LaunchPlan lp = plan_launch(d, a.workspace != nullptr, seg);
-  if (a.seg_mass != nullptr && a.workspace_bytes < seg_ws_bytes(lp, a.n_seg)) lp = plan_launch(d, false, true);
-  const int64_t total = (int64_t)d.batch * d.heads * (lp.qt_ref + lp.qt_tgt);
-  if (total > 0x7fffffff) return fail(RA_EUNSUPPORTED, "joint_attn: problem too large for one launch");
-  if (a.workspace != nullptr) {
-    if (a.workspace_bytes < lp.ws_bytes)
-      return fail(RA_EWORKSPACE, "joint_attn: workspace needs %zu bytes (got %zu)", lp.ws_bytes, a.workspace_bytes);
-    if ((reinterpret_cast<uintptr_t>(a.workspace) & 15) != 0)
-      return fail(RA_EUNSUPPORTED, "joint_attn: workspace must be 16-byte aligned");
-  }
-  p.qt_ref = (int32_t)lp.qt_ref;
-  p.qt_tgt = (int32_t)lp.qt_tgt;
-  p.total_tiles = (int32_t)total;
-  p.bm = lp.bm;
-  p.plan[0] = lp.plan[0];
-  p.plan[1] = lp.plan[1];
-  p.part_o = static_cast<float*>(a.workspace);
-  p.part_st = lp.ws_bytes ? reinterpret_cast<float4*>(static_cast<char*>(a.workspace) + lp.part_o_bytes) : nullptr;
-  p.part_lo = lp.ws_bytes ? reinterpret_cast<float*>(p.part_st + lp.items * lp.bm) : nullptr;
-  p.part_seg = lp.ws_bytes && a.seg_mass ? reinterpret_cast<float*>(static_cast<char*>(a.workspace) + lp.ws_bytes)
-                                         : nullptr;
   if (seg) {
     p.n_seg = a.n_seg;
     for (int i = 0; i < a.n_seg; ++i) {
@@ -388,8 +232,49 @@ ra_status refadapt_joint_attn(const ra_attn_desc* desc, const ra_attn_args* args
   }
 
   const hipStream_t st = static_cast<hipStream_t>(stream);
-  const hipError_t e = d.dtype == RA_BF16 ? launch_attn_bf16(p, d.head_dim, st) : launch_attn_f32(p, d.head_dim, st);
-  return launch_status(e, "joint_attn");
+  const int64_t bh = (int64_t)d.batch * d.heads;
+  if (d.dtype == RA_F32) {
+    const int64_t tiles = bh * ((ref_queries ? ((int64_t)d.n_ref + kAttnF32BM - 1) / kAttnF32BM : 0) +
+                                ((int64_t)d.n_tgt + kAttnF32BM - 1) / kAttnF32BM);
+    if (tiles > 0x7fffffff) return fail(RA_EUNSUPPORTED, "joint_attn: problem too large for one launch");
+    if ((reinterpret_cast<uintptr_t>(a.workspace) & 15) != 0)
+      return fail(RA_EUNSUPPORTED, "joint_attn: workspace must be 16-byte aligned");
+    p.qt_ref = ref_queries ? 1 : 0;
+    return launch_status(launch_attn_f32(p, d.head_dim, st), "joint_attn");
+  }
+
+  // Per-segment masses split key ranges only when the workspace also holds the per-segment
+  // partials; with a smaller workspace the launch runs whole query tiles.
+  const PlanShape shape = plan_shape(d);
+  bool split = a.workspace != nullptr;
+  LaunchPlans plans = plan_launch(shape, split);
+  if (split && a.seg_mass != nullptr && a.workspace_bytes < launch_seg_ws_bytes(plans, mode, d.head_dim, a.n_seg)) {
+    split = false;
+    plans = plan_launch(shape, split);
+  }
+  const int size = launch_size(plans, mode, d.head_dim, split ? a.workspace_bytes : 0);
+  const QueryPlan &all = plans.all[size], &tgt = plans.tgt[size], &q = mode.all ? all : tgt;
+  if (bh * (q.qt_ref + q.qt_tgt) > 0x7fffffff)
+    return fail(RA_EUNSUPPORTED, "joint_attn: problem too large for one launch");
+  const size_t need = plans.ws_bytes(0, mode.all, mode.tgt, d.head_dim);
+  if (a.workspace != nullptr) {
+    if (a.workspace_bytes < need)
+      return fail(RA_EWORKSPACE, "joint_attn: workspace needs %zu bytes (got %zu)", need, a.workspace_bytes);
+    if ((reinterpret_cast<uintptr_t>(a.workspace) & 15) != 0)
+      return fail(RA_EUNSUPPORTED, "joint_attn: workspace must be 16-byte aligned");
+  }
+  p.qt_ref = (int32_t)q.qt_ref;
+  p.qt_tgt = (int32_t)q.qt_tgt;
+  p.bm = q.bm;
+  p.plan[0] = q.plan;
+  p.plan[1] = mode.tgt ? tgt.plan : q.plan;
+  const int64_t items = std::max(q.items, mode.tgt ? tgt.items : 0);
+  char* const ws = items > 0 ? static_cast<char*>(a.workspace) : nullptr;
+  p.part_o = reinterpret_cast<float*>(ws);
+  p.part_st = ws ? reinterpret_cast<float4*>(ws + part_o_bytes(items, q.bm, d.head_dim)) : nullptr;
+  p.part_lo = ws ? reinterpret_cast<float*>(p.part_st + items * q.bm) : nullptr;
+  p.part_seg = ws && a.seg_mass ? reinterpret_cast<float*>(ws + items_ws_bytes(items, q.bm, d.head_dim)) : nullptr;
+  return launch_status(launch_attn_bf16(p, d.head_dim, st), "joint_attn");
 }
 
 size_t refadapt_q_change_workspace_size(int32_t batch, int32_t heads, int32_t n_tgt, int32_t head_dim) {

@@ -35,6 +35,7 @@
 #include <algorithm>
 
 #include "internal.h"
+#include "plan.h"
 
 namespace refadapt {
 namespace {
@@ -490,65 +491,21 @@ hipError_t launch(const AttnParams& p, hipStream_t stream) {
   return hipSuccess;
 }
 
-// The split of a launch. Every workgroup of QW query subtiles costs QW units of work, so a
-// launch of W workgroups takes about ceil(W / CUs) * QW units of the slower CUs' time: few
-// subtiles per workgroup (and so more key groups) spread a small launch over more CUs and waste
-// less of the last round, many share a K/V tile between more wavefronts. `lone` and `full` are
-// the measured time per unit of each shape with one workgroup on a CU and with several, relative
-// to (QW 4, several): 16.5 ns per key at head dim 128.
-//   us, shapes QW 4 / 2 / 1:  24 heads, 1101 + 1024, all queries 558 / 584 / 596; target queries
-//   283 / 278 / 282; 48 heads of 64, 2000 + 1900, target 804 / 885 / 981; 6 heads, 700 + 500, all
-//   96 / 63 / 68; 2 heads, 2000 + 100, target 163 / 104 / 54; 2 heads of 64, 256 + 256, all
-//   26 / 19 / 12.
-// Where two shapes are estimated within a few percent (the first launch takes QW 2) fewer keys per
-// sum also mean a smaller error: 9.2e-7 / 7.1e-7 / 5.8e-7 there.
-// The choice weighs the launch with and without the reference queries alike and does not depend
-// on which of the two this is, so target rows are summed in the same order in both.
-struct Split {
-  int qw;
-  double lone, full;
-};
-constexpr Split kSplits[] = {{4, 1.18, 1.0}, {2, 1.45, 1.11}, {1, 1.57, 1.25}};
-constexpr int kLongKeys = 512;
-
-int choose_split(const AttnParams& p, int64_t cus) {
-  const int64_t bh = (int64_t)p.B * p.H;
-  int best = 4;
-  double best_cost = 0.0;
-  for (const Split& s : kSplits) {
-    const int64_t bq = 16 * s.qw;
-    const int64_t tgt = bh * ((p.n_tgt + bq - 1) / bq), all = tgt + bh * ((p.n_ref + bq - 1) / bq);
-    double cost = 1.0;
-    for (const int64_t w : {tgt, all}) cost *= (double)((w + cus - 1) / cus * s.qw) * (w <= cus ? s.lone : s.full);
-    if (best_cost == 0.0 || cost < best_cost) {
-      best = s.qw;
-      best_cost = cost;
-    }
-  }
-  return best;
-}
-
 template <int D>
 hipError_t launch_dim(const AttnParams& p, hipStream_t stream) {
   const int dev_cus = attn_bf16_slots(D, kAttnBf16BM).cus;
   const int64_t cus = dev_cus > 0 ? dev_cus : 256;
-  switch (choose_split(p, cus)) {
+  const F32Split sp = f32_split((int64_t)p.B * p.H, p.n_ref, p.n_tgt, cus);
+  switch (sp.subtiles) {
     case 4: return launch<D, 4, 4, 32>(p, stream);
     case 2: return launch<D, 4, 2, 16>(p, stream);
-    default: break;
+    default: return sp.wavefronts == 8 ? launch<D, 8, 1, 16>(p, stream) : launch<D, 4, 1, 16>(p, stream);
   }
-  // One subtile per workgroup: four key groups, or eight where the launch leaves the CUs one
-  // workgroup each and the groups still have several key tiles (2 heads, 2000 + 100 keys 54
-  // against 58 us, one head of 64 with 2048 + 2048 keys 57 against 68; 64 + 64 keys 9.5 against 8.1).
-  const int64_t sub = (int64_t)p.B * p.H * ((p.n_tgt + 15) / 16);
-  if (sub <= cus && (int64_t)p.n_ref + p.n_tgt >= kLongKeys) return launch<D, 8, 1, 16>(p, stream);
-  return launch<D, 4, 1, 16>(p, stream);
 }
 
 }  // namespace
 
 hipError_t launch_attn_f32(const AttnParams& p, int head_dim, hipStream_t stream) {
-  if (p.total_tiles <= 0) return hipSuccess;
   return head_dim == 128 ? launch_dim<128>(p, stream) : launch_dim<64>(p, stream);
 }
 

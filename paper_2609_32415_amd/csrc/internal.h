@@ -44,9 +44,8 @@ struct AttnParams {
   const int32_t* decision;  // KV_DEVICE only
   unsigned long long* clock_probe;  // [2] shader cycles, 100 MHz ticks (added to), or null
   int32_t B, H, n_ref, n_tgt;
-  int32_t qt_ref;       // query tiles per (b, h) over reference rows (0 when they do not attend)
-  int32_t qt_tgt;       // query tiles per (b, h) over target rows
-  int32_t total_tiles;  // B * H * (qt_ref + qt_tgt) = grid size
+  int32_t qt_ref;  // bf16: query tiles per (b, h) over reference rows; both: 0 when they do not attend
+  int32_t qt_tgt;  // bf16: query tiles per (b, h) over target rows
   int32_t kvsrc;
   int32_t block0;  // fp32 path: this launch's first workgroup among those of the call
   float sc_log2;  // softmax scale * log2(e)

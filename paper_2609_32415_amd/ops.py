@@ -214,9 +214,10 @@ def joint_attn(
 
 
 def attn_workspace(q_tgt, n_ref, qset="target", kvsrc="fresh", n_seg_mass=0):
-    """Preallocated key-split workspace for ``joint_attn`` calls of this shape on
-    ``q_tgt``'s device (False when the library would not split); ``n_seg_mass``
-    segments with ``seg_mass`` need the larger segment workspace."""
+    """Preallocated key-split workspace for ``joint_attn`` calls of this shape and query
+    set, whatever their ``kvsrc``, on ``q_tgt``'s device (False when the library would not
+    split); that of ``kvsrc="device"`` serves both query sets. ``n_seg_mass`` segments with
+    ``seg_mass`` need the larger segment workspace."""
     B, H, n_tgt, D = q_tgt.shape
     desc = L.ra_attn_desc(B, H, D, n_ref, n_tgt, _DTYPES[q_tgt.dtype], 0.0, _QSET[qset], _KVSRC[kvsrc])
     with torch.cuda.device(q_tgt.device):
