@@ -179,7 +179,7 @@ def joint_attn(
     shp_t = (B, H, n_tgt, D)
     shp_r = (B, H, n_ref, D)
     desc = (B, H, D, n_ref, n_tgt, _DTYPES[dt],
-            ctypes.c_float(scale).value if scale else 0.0, _QSET[qset], _KVSRC[kvsrc])
+            ctypes.c_float(float(scale)).value if scale else 0.0, _QSET[qset], _KVSRC[kvsrc])
     if workspace is None:
         if smass_t is not None:
             nbytes = L.refadapt_joint_attn_seg_workspace_size(L.ra_attn_desc(*desc), n_seg)
