@@ -256,7 +256,7 @@ ra_status refadapt_joint_attn(const ra_attn_desc* desc, const ra_attn_args* args
   const QueryPlan &all = plans.all[size], &tgt = plans.tgt[size], &q = mode.all ? all : tgt;
   if (bh * (q.qt_ref + q.qt_tgt) > 0x7fffffff)
     return fail(RA_EUNSUPPORTED, "joint_attn: problem too large for one launch");
-  const size_t need = plans.ws_bytes(0, mode.all, mode.tgt, d.head_dim);
+  const size_t need = plans.ws_bytes(0, mode, d.head_dim);
   if (a.workspace != nullptr) {
     if (a.workspace_bytes < need)
       return fail(RA_EWORKSPACE, "joint_attn: workspace needs %zu bytes (got %zu)", need, a.workspace_bytes);

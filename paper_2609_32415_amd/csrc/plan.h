@@ -64,7 +64,8 @@ inline SplitPlan plan_split(int64_t tiles, int nt, AttnSlots sl, int head_dim, i
 }
 
 // Estimated time (us) of a plan on workgroups of bm query rows, to choose between the two
-// workgroup sizes. Time of one key tile in a round, measured per head dim with few workgroups
+// workgroup sizes. (plan_split compares chunk counts on one size, where its units cancel; here the
+// two sizes' rates have to be right against each other.) Time of one key tile in a round, measured per head dim with few workgroups
 // (one a CU at most, `lone`) and with a full round (`full`): 256-row workgroups keep a CU to
 // themselves and share a K/V tile between eight wavefronts; 128-row ones run two a CU, or one at
 // less time a tile, for twice the K/V traffic.
@@ -72,7 +73,7 @@ struct TileTime {
   double lone, full;
 };
 constexpr double kStartTiles = 2.0;  // start-up and drain of a workgroup, in key tiles
-constexpr double kMergeUs = 5.0;
+constexpr double kMergeUs = 5.0;     // the merge's launch; its traffic is charged by bytes
 
 inline TileTime tile_time(int head_dim, int bm) {
   if (bm == kAttnBf16BM) return head_dim == 128 ? TileTime{1.27, 1.62} : TileTime{1.02, 1.07};
@@ -84,7 +85,9 @@ inline double plan_us(const SplitPlan& pl, int nt, AttnSlots sl, int head_dim, i
   const int64_t cus = sl.cus, slots = cus * sl.per_cu;
   const auto rounds = [&](int64_t items, double len) {
     const int64_t full = items / slots, last = items - full * slots;
-    // a partly filled last round draws less power and runs at a higher clock
+    // A partly filled last round draws less power and runs at a higher clock: from `lone` with few
+    // workgroups to `full`, or, with one 128-row workgroup a CU, to 0.2 us above `lone` (fitted, as
+    // the rates, to the launches named at prefers_small).
     const double top = bm == kAttnBf16BM ? tt.full : tt.lone + 0.2;
     const double part = last > cus ? tt.full : last > 0 ? tt.lone + (top - tt.lone) * (double)last / (double)cus : 0.0;
     return len * ((double)full * tt.full + part);
@@ -138,34 +141,46 @@ inline QueryPlan plan_queries_bm(const PlanShape& s, bool ref_queries, bool spli
   return q;
 }
 
-// A launch's query sets on both workgroup sizes: target rows, and reference and target rows.
+// What a launch of one K/V mode runs: the query sets it may hold (a device-decided launch both).
+struct LaunchMode {
+  bool all, tgt;  // reference and target rows; target rows alone
+  bool seg;       // reference segments
+};
+
+// The two query sets on both workgroup sizes.
 struct LaunchPlans {
   QueryPlan tgt[2], all[2];  // [0]: 256 rows, [1]: 128 rows
+  bool split;                // key ranges may be split
 
-  // A launch runs workgroups of 128 query rows where the estimates for the target queries and for
-  // all queries say together (their product) that these are 5% faster (the estimates' own error),
-  // else of 256: launches of few tiles, which leave CUs idle or one workgroup each. Measured, us,
-  // 256 against 128 rows: 4 heads, 300 + 256 tokens, all queries 21.8 / 15.9; 24 heads, 1024 target
-  // queries over 2048 keys 43.6 / 38.3; 12 heads, 700 + 800, all 40.8 / 30.5; 24 heads, 2095 + 1009,
-  // all 133 / 135; 24 heads, 4352 + 4096, all 755 / 778. Whole (unsplit) rows are summed in the same
-  // order in both. The choice is the same for both query sets, wherever the K/V come from and whoever
-  // decides: a device-decided launch gives the bits of the explicit launch of the same queries. (Over
-  // 44 shapes of 1 to 48 heads and 64 to 8192 tokens explicit launches take 0.996 and 0.999, and
-  // device-decided ones 0.981 and 0.997 of the time with a choice per mode.) The segment kernel runs
-  // 256 rows only.
-  bool prefers_small() const {
-    const double big = tgt[0].us * all[0].us, small = tgt[1].us * all[1].us;
-    return small > 0.0 && small < 0.95 * big;
+  // A launch runs workgroups of 128 query rows where the estimates say that they are 5% faster
+  // (the estimates' own error), else of 256: launches of few tiles, which leave CUs idle or one
+  // workgroup each. Measured, us, 256 against 128 rows: 4 heads, 300 + 256 tokens, all queries
+  // 21.8 / 15.9; 24 heads, 1024 target queries over 2048 keys 43.6 / 38.3; 12 heads, 700 + 800, all
+  // 40.8 / 30.5; 24 heads, 2095 + 1009, all 133 / 135; 24 heads, 4352 + 4096, all 755 / 778. The
+  // segment kernel runs 256 rows only.
+  // Where key ranges may be split the estimates are those of the target queries and of all queries
+  // together (their product), so that the choice is the same for both, wherever the K/V come from
+  // and whoever decides: a device-decided launch gives the bits of the explicit launch of the same
+  // queries. (Over 44 shapes of 1 to 48 heads and 64 to 8192 tokens explicit launches of all and of
+  // target queries take 0.99 and 0.98, device-decided ones 0.99 and 0.97 of the time with a choice
+  // per mode.) Whole rows are summed in the same order on both sizes: without splits the launch's
+  // own sets count (24 heads of 64, 1500 + 700, all queries 41.8 us; 45.0 by both sets).
+  bool prefers_small(LaunchMode m) const {
+    double big = 1.0, small = 1.0;
+    if (split || m.tgt) big *= tgt[0].us, small *= tgt[1].us;
+    if (split || m.all) big *= all[0].us, small *= all[1].us;
+    return !m.seg && small > 0.0 && small < 0.95 * big;
   }
-  // Workspace of the given query sets' split items on one workgroup size.
-  size_t ws_bytes(int size, bool with_all, bool with_tgt, int head_dim) const {
-    const int bm = tgt[size].bm;
-    return items_ws_bytes(std::max(with_all ? all[size].items : 0, with_tgt ? tgt[size].items : 0), bm, head_dim);
+  // Workspace of the launch's split items on one workgroup size.
+  size_t ws_bytes(int size, LaunchMode m, int head_dim) const {
+    const int64_t items = std::max(m.all ? all[size].items : 0, m.tgt ? tgt[size].items : 0);
+    return items_ws_bytes(items, tgt[size].bm, head_dim);
   }
 };
 
 inline LaunchPlans plan_launch(const PlanShape& s, bool split) {
   LaunchPlans l;
+  l.split = split;
   for (int i = 0; i < 2; ++i) {
     const int bm = i == 0 ? kAttnBf16BM : kAttnBf16SmallBM;
     l.tgt[i] = plan_queries_bm(s, false, split, bm);
@@ -174,17 +189,11 @@ inline LaunchPlans plan_launch(const PlanShape& s, bool split) {
   return l;
 }
 
-// What a launch of one K/V mode runs: the query sets it may hold (a device-decided launch both).
-struct LaunchMode {
-  bool all, tgt;  // reference and target rows; target rows alone
-  bool seg;       // reference segments
-};
-
-// Workspace to ask for, the same for every K/V source of the query sets: what the plan needs that the
-// launch prefers, or the one on 256 rows where that is more, with which a launch runs too.
+// Workspace to ask for, the same for every K/V source of the query sets: what the plan needs that a
+// launch without segments prefers, or the one on 256 rows where that is more, with which it runs too.
 inline size_t launch_ws_bytes(const LaunchPlans& l, LaunchMode m, int head_dim) {
-  const size_t big = l.ws_bytes(0, m.all, m.tgt, head_dim);
-  return l.prefers_small() ? std::max(big, l.ws_bytes(1, m.all, m.tgt, head_dim)) : big;
+  const size_t big = l.ws_bytes(0, m, head_dim);
+  return l.prefers_small({m.all, m.tgt, false}) ? std::max(big, l.ws_bytes(1, m, head_dim)) : big;
 }
 
 // Workspace with which a launch with per-segment masses splits key ranges: that of the launch
@@ -197,7 +206,7 @@ inline size_t launch_seg_ws_bytes(const LaunchPlans& l, LaunchMode m, int head_d
 // The workgroup size (index) of a launch with a workspace of ws_bytes: the preferred one if its
 // partials fit.
 inline int launch_size(const LaunchPlans& l, LaunchMode m, int head_dim, size_t ws_bytes) {
-  return !m.seg && l.prefers_small() && l.ws_bytes(1, m.all, m.tgt, head_dim) <= ws_bytes ? 1 : 0;
+  return l.prefers_small(m) && l.ws_bytes(1, m, head_dim) <= ws_bytes ? 1 : 0;
 }
 
 // ---- fp32: query subtiles per workgroup and key groups inside it

@@ -24,9 +24,9 @@ int main() {
     const LaunchPlans l = plan_launch(shape, true), whole = plan_launch(shape, false);
     for (const bool all : {true, false}) {
       const LaunchMode m{all, !all, false};
-      const QueryPlan& q = (all ? l.all : l.tgt)[l.prefers_small()];
+      const QueryPlan& q = (all ? l.all : l.tgt)[l.prefers_small(m)];
       std::printf("%d %d %d %d %zu %zu %d%s", q.bm, q.plan.whole, q.plan.split_tiles, q.plan.chunks,
-                  launch_ws_bytes(l, m, D), launch_seg_ws_bytes(l, m, D, 3), whole.tgt[whole.prefers_small()].bm,
+                  launch_ws_bytes(l, m, D), launch_seg_ws_bytes(l, m, D, 3), whole.tgt[whole.prefers_small(m)].bm,
                   all ? " " : "\n");
     }
   }
