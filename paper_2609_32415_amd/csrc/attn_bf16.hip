@@ -32,8 +32,9 @@
 // One workgroup of 256 rows (or two of 128) fills a CU with two wavefronts per SIMD (at most
 // 256 vector registers per lane each): while one wavefront forms probabilities the other
 // keeps the matrix core busy, and a workgroup's wavefronts share every K/V tile
-// in LDS. At head dim 64 a third wavefront per SIMD fits the registers and gave nothing: the
-// loop is bound by the instructions it issues and the power they take, not by latency.
+// in LDS. The loop is bound by the instructions it issues and the power they take more than by
+// latency: at head dim 64, with 193 to 200 registers, both workgroup sizes took the same time on
+// large launches.
 //
 // Online softmax in the exp2 domain without a per-tile row max: probabilities
 // are formed against the running max m, and a lane's partial row sum bounds
@@ -485,9 +486,10 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
       if (kc.t < j1) issue_load(std::true_type{}, kc, kb_cur);
       issue_load(std::false_type{}, vc, vb_cur);
     };
-    // Head dim 64: which wavefront of a SIMD wins issue ties alternates between the two halves, so
-    // the pair finishes a tile together instead of one idling at the barrier (-1%; at head dim
-    // 128 it made no difference).
+    // Head dim 64, 256 rows: which wavefront of a SIMD wins issue ties alternates between the two
+    // halves, so the pair finishes a tile together instead of one idling at the barrier (-1%; at head
+    // dim 128 it made no difference). A SIMD's two wavefronts of 128-row workgroups share no barrier.
+    constexpr bool PRIO = D == 64 && BM == kAttnBf16BM;
     const bool partner = wave_u >= NW / 2;
     auto set_prio = [](bool high) __attribute__((always_inline)) {
       if (high)
@@ -552,7 +554,7 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
     };
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb) s_next[mb] = f32x16{};
-    if constexpr (D == 64) set_prio(partner);
+    if constexpr (PRIO) set_prio(partner);
     bf16x8 ka[4], va[3];
     if constexpr (PV > 0) {
       va[0] = v_operand(0);
@@ -566,7 +568,7 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnParams p) {
     for (int i = 0; i < NS; ++i) {
       if (i == NS / 2) {
         issue_loads();
-        if constexpr (D == 64) set_prio(!partner);
+        if constexpr (PRIO) set_prio(!partner);
       }
       if (i < PV) {
         const int s2 = i / DB;
@@ -958,7 +960,9 @@ template __global__ void attn_bf16_kernel<64, 256, true, true, false>(AttnParams
 template <int D, int BM>
 hipError_t launch_plain(const AttnParams& p, dim3 grid, hipStream_t stream) {
   // The instance with both key loops only where a launch has rows for the bare one: its larger
-  // code costs the others up to 1% (reuse launches 0.3%, launches of a few tiles 1%).
+  // code and scalar-register spills (67 against 34 at head dim 128) cost the others up to 1% (reuse
+  // launches 0.3%, launches of a few tiles 1%). A device-decided launch takes it for the rows that
+  // the host cannot rule out, and pays that where the decision is REUSE.
   const bool bare = (p.qt_ref > 0 && !p.mass_refq) || !(p.mass_tgt || p.lse_tgt);
   return bare ? launch_kernel(attn_bf16_kernel<D, BM, false, false, true>, grid, dim3(2 * BM), 0, stream, p)
               : launch_kernel(attn_bf16_kernel<D, BM, false, false, false>, grid, dim3(2 * BM), 0, stream, p);
