@@ -2,7 +2,7 @@
 sizes where it can go wrong, against the fp64 oracle.
 
 The split follows from (batch, heads, n_ref, n_tgt) on a 256-CU device; the shapes below reach
-each one (named in the id) with row counts around the 16-row subtiles and key counts around the
+each one (named in the id, asserted by test_attn_plans.py) with row counts around the 16-row subtiles and key counts around the
 16- and 32-key tiles, key groups without keys or without reference keys included."""
 
 import numpy as np

@@ -23,9 +23,9 @@ def test_adjacent_change(T, nb, bh):
     np.testing.assert_allclose(got, want, rtol=2.0 ** -23)  # fp64 inside, one rounding of the result
 
 
-# rows -> chunks per head at head_dim 128: 1 -> 1, 300 -> 3, 4096 -> 32, 9000 -> 64
+# rows -> chunks per head at head_dim 128: 1 -> 1, 48 -> 3, 300 -> 8, 4096 -> 32, 9000 -> 64
 @pytest.mark.parametrize("H", [1, 31, 32, 33, 65])
-@pytest.mark.parametrize("n", [1, 300, 4096, 9000])
+@pytest.mark.parametrize("n", [1, 48, 300, 4096, 9000])
 def test_second_passes(H, n):
     from paper_2609_32415_amd import ops
 
