@@ -51,8 +51,9 @@
 // applied to V sum to one: with the fp32 sum, the rounding of a dominant
 // probability (relative error up to 2^-8) moved the output by as much of V.
 // Rows that want neither mass nor log-sum-exp ("bare": the reference rows of most launches)
-// skip the fp32 sums and take the bound test on the rounded one: 2.78 -> 2.71 ms at 24 heads of
-// 128, 12544 of the 16640 queries bare; 467 -> 455 us at 24 heads of 64, 4352 of 8448.
+// skip the fp32 sums; their rounded sum finds the few tiles near the bound, for which the fp32 one
+// is formed, so that o has the same bits either way: 2.78 -> 2.71 ms at 24 heads of 128, 12544 of
+// the 16640 queries bare; 467 -> 455 us at 24 heads of 64, 4352 of 8448.
 //
 // Split statistics for the reference mass (paper Sec. 3.2, directional
 // exposure): after the last reference tile the running (max, sum) pair is

@@ -41,8 +41,9 @@ CODEGEN_FLAGS = [
     # MFMA accumulators in ordinary vector registers: the softmax reads the
     # score tiles directly instead of copying them out of AGPRs every tile.
     "-mllvm", "-amdgpu-mfma-vgpr-form",
-    # The scheduler's register-pressure tracking that spills fewer scalar registers to
-    # vector lanes in the attention loop (80 instead of 109; about -0.5% launch time).
+    # The scheduler's register-pressure tracking that spills fewer scalar registers to vector
+    # lanes in the bf16 attention (17 to 105 by instance; with two phases per key tile and one
+    # instance 80 instead of 109, about -0.5% launch time).
     "-mllvm", "-amdgpu-use-amdgpu-trackers=1",
 ]
 

@@ -217,12 +217,14 @@ inline int launch_size(const LaunchPlans& l, LaunchMode m, int head_dim, size_t 
 // less of the last round, many share a K/V tile between more wavefronts. `lone` and `full` are
 // the measured time per unit of each shape with one workgroup on a CU and with several, relative
 // to (QW 4, several): 16.5 ns per key at head dim 128.
-//   us, shapes QW 4 / 2 / 1:  24 heads, 1101 + 1024, all queries 558 / 584 / 596; target queries
-//   283 / 278 / 282; 48 heads of 64, 2000 + 1900, target 804 / 885 / 981; 6 heads, 700 + 500, all
-//   96 / 63 / 68; 2 heads, 2000 + 100, target 163 / 104 / 54; 2 heads of 64, 256 + 256, all
-//   26 / 19 / 12.
-// Where two shapes are estimated within a few percent (the first launch takes QW 2) fewer keys per
-// sum also mean a smaller error: 9.2e-7 / 7.1e-7 / 5.8e-7 there.
+//   us, shapes QW 4 / 2 / 1:  24 heads, 1101 + 1024, all queries 584 / 600 / 602; target queries
+//   296 / 274 / 285; 48 heads of 64, 2000 + 1900, target 829 / 887 / 962; 8 heads, 2048 + 2048, all
+//   558 / 629 / 705; 6 heads, 700 + 500, all 101 / 66 / 70; 2 heads, 2000 + 100, target
+//   171 / 107 / 54; 2 heads of 64, 256 + 256, all 28 / 20 / 12.
+// The first launch takes QW 2: counting whole rounds charges QW 4's 384 target workgroups two,
+// though two share a CU, and the estimates (128 / 103 / 122) are further apart than the times; QW 2
+// is 3% slower than QW 4 there on all queries and 7% faster on the target ones. Fewer keys per sum
+// also mean a smaller error: 9.2e-7 / 7.2e-7 / 5.9e-7 there.
 // The choice weighs the launch with and without the reference queries alike and does not depend
 // on which of the two this is, so target rows are summed in the same order in both.
 struct F32Cost {
