@@ -152,24 +152,24 @@ struct LaunchPlans {
   QueryPlan tgt[2], all[2];  // [0]: 256 rows, [1]: 128 rows
   bool split;                // key ranges may be split
 
-  // A launch runs workgroups of 128 query rows where the estimates say that they are 5% faster
-  // (the estimates' own error), else of 256: launches of few tiles, which leave CUs idle or one
+  // A launch runs workgroups of 128 query rows where the estimates say by more than their own error
+  // (3 to 5%) that these are faster, else of 256: launches of few tiles, which leave CUs idle or one
   // workgroup each. Measured, us, 256 against 128 rows: 4 heads, 300 + 256 tokens, all queries
   // 21.8 / 15.9; 24 heads, 1024 target queries over 2048 keys 43.6 / 38.3; 12 heads, 700 + 800, all
   // 40.8 / 30.5; 24 heads, 2095 + 1009, all 133 / 135; 24 heads, 4352 + 4096, all 755 / 778. The
   // segment kernel runs 256 rows only.
   // Where key ranges may be split the estimates are those of the target queries and of all queries
-  // together (their product), so that the choice is the same for both, wherever the K/V come from
+  // together (3% each), so that the choice is the same for both, wherever the K/V come from
   // and whoever decides: a device-decided launch gives the bits of the explicit launch of the same
   // queries. (Over 44 shapes of 1 to 48 heads and 64 to 8192 tokens explicit launches of all and of
   // target queries take 0.99 and 0.98, device-decided ones 0.99 and 0.97 of the time with a choice
   // per mode.) Whole rows are summed in the same order on both sizes: without splits the launch's
   // own sets count (24 heads of 64, 1500 + 700, all queries 41.8 us; 45.0 by both sets).
   bool prefers_small(LaunchMode m) const {
-    double big = 1.0, small = 1.0;
+    double big = split ? 0.97 * 0.97 : 0.95, small = 1.0;
     if (split || m.tgt) big *= tgt[0].us, small *= tgt[1].us;
     if (split || m.all) big *= all[0].us, small *= all[1].us;
-    return !m.seg && small > 0.0 && small < 0.95 * big;
+    return !m.seg && small > 0.0 && small < big;
   }
   // Workspace of the launch's split items on one workgroup size.
   size_t ws_bytes(int size, LaunchMode m, int head_dim) const {
